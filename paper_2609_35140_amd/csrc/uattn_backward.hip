@@ -13,13 +13,13 @@
 // that depends on nothing but its own sequence:
 //   bwd_prep_kernel  D_i and lse_i * log2(e) of every (token, q head), written
 //                    head-major into the workspace;
-//   bwd_dkdv_kernel  one workgroup per (128-key tile, sequence, kv head); wave w
-//                    owns keys 32w .. 32w+31 and keeps their K and V operands and
-//                    the dK^T, dV^T accumulators in registers while it walks the
-//                    group's q heads, then the 64-query tiles at or after its
-//                    keys, in ascending order (S = Q K^T with the keys as MFMA
-//                    columns, so P and dS already sit in the layout the dV^T and
-//                    dK^T products consume);
+//   bwd_dkdv_kernel  one workgroup per (128-key tile, sequence, kv head); waves w
+//                    and w+4 own keys 32w .. 32w+31, one with the K operands and the
+//                    dV^T accumulator in registers, the other with V and dK^T, and
+//                    walk the 64-query tiles from the sequence's end down to their
+//                    keys, every q head of the group at each tile (S = Q K^T with
+//                    the keys as MFMA columns, so P and dS already sit in the
+//                    layout the dV^T and dK^T products consume);
 //   bwd_dq_kernel    one workgroup per (256-query tile, sequence, q head), laid
 //                    out as the forward (queries as MFMA columns): walks the
 //                    64-key tiles up to each wave's diagonal in ascending order.
@@ -146,6 +146,7 @@ struct BwdParams {
   __bf16* dk;
   __bf16* dv;
   int hq, hkv, group, total, num_seqs;
+  int kv_units, dq_units;  // work units of the two kernels (see xcd_unit)
   float c, scale;
 };
 
@@ -190,25 +191,147 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(BwdParams p) {
 
 // ---------------------------------------------------------------------------
 // dK, dV
+//
+// 8 waves; waves w and w+4 share a SIMD (as in the forward) and the keys
+// 32*(w%4) .. +31 of the workgroup's 128.  Wave w < 4 forms S and P and
+// accumulates dV; wave w+4 forms dP and dS (from P, passed in fp32 through LDS)
+// and accumulates dK.  One wave doing both needs the two accumulators (128
+// registers), both key operands (64) and both score tiles (64), which leaves
+// one wave on a SIMD and nothing to run beside its matrix instructions.
+//
+// Ping-pong, as the forward: a step of a wave is a matrix phase (the products
+// of tile t-1's weights, then the scores of tile t) and a vector phase (the
+// weights of tile t), each in a slot opened by a workgroup barrier, the waves
+// 4-7 one slot behind:
+//   slot 2t    waves 0-3: dV += dO(t-1)^T P(t-1), S(t)    waves 4-7: dS(t-1)
+//   slot 2t+1  waves 0-3: P(t) -> registers and LDS       waves 4-7: dK += Q(t-1)^T dS(t-1), dP(t)
+// so P(t) is written in slot 2t+1 and read in slot 2t+2.  Tiles t-1 and t are
+// both read during a step, so the tiles move through a ring of three stages:
+// waves 4-7, whose vector phase is the shorter one (no exponentials), load
+// tile t+2 in slot 2t+2 over tile t-1, whose last readers ended in slot 2t+1,
+// and wait for it before slot 2t+4, the first that reads it.
+//
+// Order: query tiles from the sequence's end down, the group's heads inside.
+// Every key tile of a (sequence, kv head) starts at the same query tile and
+// keeps step with the others, so the tiles that one of them brings into the
+// XCD's L2 serve all (from the diagonal up, heads outside, 86% of the L2
+// requests missed and the misses set the time: 4.2 ms against 3.0 in the
+// measurement below).
+//
+// What bounds it: the matrix phases (64 products, 1024 cycles at the issue
+// rate, against about 1.8 times that measured) with the other wave's vector
+// work beside them.  8 sequences of 512-8192 tokens, 32/8 heads, d = 128
+// (2.8 TFLOP in these four products): 4.85 ms with one wave per SIMD and
+// everything in it, 2.5-2.7 ms so (1.05-1.1 PFLOP/s).  Loads by waves 0-3 in
+// their matrix phase 2.8, in their vector phase 2.6 ms; the next phase's
+// first operands read before the barrier 2.7 ms.
 // ---------------------------------------------------------------------------
-constexpr int kKvWaves = 4;
-constexpr int kKeysPerWave = 32;
-constexpr int kKeyTile = kKvWaves * kKeysPerWave;  // keys per workgroup
+constexpr int kKvPairs = 4;                        // wave pairs, each with its own keys
+constexpr int kKvWaves = 2 * kKvPairs;
+constexpr int kKeysPerPair = 32;
+constexpr int kKeyTile = kKvPairs * kKeysPerPair;  // keys per workgroup
 constexpr int kQTile = kTileKeys;                  // queries per step
+// Key tiles to a work unit (see xcd_unit): they walk the same query tiles in
+// step, so a unit's tiles come from its XCD's L2 (groups of 4, 16 and 32 were
+// within 2% of 8).
+constexpr int kKeyTileGroup = 8;
+
+// One matrix phase: acc[db][nb] += T^T w over the 64 rows of the tile at
+// `tr_tile` (kPrev), then s[qb][nb] = R x over the rows of the tile at `row_tile`
+// (kScores).  LDS reads run ahead of the products that use them, in a fixed
+// order, so that one wave alone keeps the matrix unit fed.  A d block or K
+// step enters the LDS address as a XOR of bits that the rest leaves clear
+// (rows of 2*D bytes, even swizzle), so one register holds each base.
+template <int D, bool kPrev, bool kScores>
+__device__ __forceinline__ void dkdv_matrix_phase(uint32_t tr_tile, uint32_t row_tile, const bf16x8 (&w)[2][2],
+                                                  const bf16x8 (&x)[2][D / 32], f32x4 (&acc)[D / 16][2],
+                                                  f32x4 (&s)[4][2], int lane) {
+  using BT = BwdTile<D>;
+  constexpr int NDB = D / 16, NST = D / 32;
+  constexpr int kAhead = 3;
+  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+  typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
+  const int g = lane >> 4, src = lane & 15;
+  const int trow = 4 * g + (src >> 2), sub = src & 3;
+  uint32_t ta = tr_tile + trow * D * 2 + 16 * ((sub >> 1) ^ BT::swz(trow)) + 8 * (sub & 1);
+  uint32_t ra = row_tile + src * D * 2 + 16 * (g ^ BT::swz(src));
+  asm volatile("" : "+v"(ta), "+v"(ra));
+  auto tread = [&](int db, bf16x8(&a)[2]) {
+    lds_s16x4* tp = reinterpret_cast<lds_s16x4*>(static_cast<uintptr_t>(ta ^ (32u * db)));
+#pragma unroll
+    for (int st = 0; st < 2; ++st) {
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(tp + (32 * st) * D / 4);
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(tp + (32 * st + 16) * D / 4);
+      const s16x4 v[2] = {lo, hi};
+      __builtin_memcpy(&a[st], v, sizeof(bf16x8));
+    }
+  };
+  auto rread = [&](int qb, bf16x8(&a)[NST]) {
+#pragma unroll
+    for (int st = 0; st < NST; ++st) {
+      const lds_bf16x8* rp = reinterpret_cast<const lds_bf16x8*>(static_cast<uintptr_t>(ra ^ (64u * st)));
+      a[st] = rp[16 * qb * D / 8];
+    }
+  };
+  bf16x8 ra_op[2][NST];
+  if constexpr (kPrev) {
+    bf16x8 tr_op[kAhead][2];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) tread(i, tr_op[i]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) {
+      bf16x8(&a)[2] = tr_op[db % kAhead];
+#pragma unroll
+      for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+        for (int st = 0; st < 2; ++st) acc[db][nb] = mfma16(a[st], w[nb][st], acc[db][nb]);
+      if (db + kAhead < NDB) tread(db + kAhead, tr_op[db % kAhead]);
+      if constexpr (kScores) {
+        if (db == NDB - 3) rread(0, ra_op[0]);
+        if (db == NDB - 1) rread(1, ra_op[1]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  } else if constexpr (kScores) {
+    rread(0, ra_op[0]);
+    rread(1, ra_op[1]);
+  }
+  if constexpr (kScores) {
+#pragma unroll
+    for (int qb = 0; qb < 4; ++qb) {
+      bf16x8(&a)[NST] = ra_op[qb & 1];
+      f32x4 r[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+      for (int st = 0; st < NST; ++st) {
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) r[nb] = mfma16(a[st], x[nb][st], r[nb]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      s[qb][0] = r[0];
+      s[qb][1] = r[1];
+      if (qb + 2 < 4) rread(qb + 2, ra_op[qb & 1]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+}
 
 template <int D>
 __global__ __launch_bounds__(kKvWaves * 64, 1) void bwd_dkdv_kernel(BwdParams p) {
   using BT = BwdTile<D>;
   constexpr int NST = D / 32, NDB = D / 16;
-  constexpr int kRpw = kQTile / kKvWaves;
-  // a stage: the Q tile, the dO tile, then 4 x 64 floats (D, lse2, and copies)
-  constexpr int kStageElems = 2 * BT::kElems + 512;
-  __shared__ __attribute__((aligned(1024))) __bf16 lds[2 * kStageElems];
+  constexpr int kRpw = kQTile / kKvPairs;  // rows of a tile that each of the waves 4-7 loads
+  // a stage: the Q tile, the dO tile, then 64 D_i and 64 lse2 floats
+  constexpr int kStageElems = 2 * BT::kElems + 256;
+  constexpr int kStages = 3;
+  __shared__ __attribute__((aligned(1024))) __bf16 lds[kStages * kStageElems];
+  __shared__ __attribute__((aligned(1024))) f32x4 pbuf[kKvPairs][8][64];  // P(t), in each lane's score layout
 
-  const int per_kt = p.num_seqs * p.hkv;
-  const int kt = blockIdx.x / per_kt;
-  const int seq = (blockIdx.x % per_kt) / p.hkv;
-  const int kvh = blockIdx.x % p.hkv;
+  const XcdUnit w = xcd_unit(blockIdx.x, kKeyTileGroup);
+  if (w.unit >= p.kv_units) return;
+  const int kt = w.unit / (p.num_seqs * p.hkv) * kKeyTileGroup + w.member;
+  const int seq = (w.unit / p.hkv) % p.num_seqs;
+  const int kvh = w.unit % p.hkv;
   int lo, L;
   seq_range(p, seq, lo, L);
   const int k0 = kt * kKeyTile;
@@ -216,154 +339,163 @@ __global__ __launch_bounds__(kKvWaves * 64, 1) void bwd_dkdv_kernel(BwdParams p)
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
+  const int pair = wave & (kKvPairs - 1);
+  const bool late = wave >= kKvPairs;                         // dP, dS, dK; one slot behind
   const int g = lane >> 4, col = lane & 15;
-  const int kw0 = k0 + kKeysPerWave * wave;
+  const int kw0 = k0 + kKeysPerPair * pair;
 
-  // B operands of this wave's keys: kf[nb][st] = K[kw0 + 16*nb + col][32*st + 8*g .. +7]
-  bf16x8 kf[2][NST], vf[2][NST];
+  // B operands of this wave's keys (K, or V in the late waves):
+  // xf[nb][st] = K[kw0 + 16*nb + col][32*st + 8*g .. +7]
+  bf16x8 xf[2][NST];
+  const __bf16* xsrc = late ? p.v : p.k;
 #pragma unroll
   for (int nb = 0; nb < 2; ++nb) {
     const int kp = kw0 + 16 * nb + col;
     if (kp < L) {
       const int64_t off = (static_cast<int64_t>(lo + kp) * p.hkv + kvh) * D + 8 * g;
 #pragma unroll
-      for (int st = 0; st < NST; ++st) {
-        kf[nb][st] = *reinterpret_cast<const bf16x8*>(p.k + off + 32 * st);
-        vf[nb][st] = *reinterpret_cast<const bf16x8*>(p.v + off + 32 * st);
-      }
+      for (int st = 0; st < NST; ++st) xf[nb][st] = *reinterpret_cast<const bf16x8*>(xsrc + off + 32 * st);
     } else {
 #pragma unroll
       for (int st = 0; st < NST; ++st)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          kf[nb][st][e] = static_cast<__bf16>(0.0f);
-          vf[nb][st][e] = static_cast<__bf16>(0.0f);
-        }
+        for (int e = 0; e < 8; ++e) xf[nb][st][e] = static_cast<__bf16>(0.0f);
     }
   }
 
   const int nqt = (L + kQTile - 1) / kQTile;
-  const int qt0 = k0 / kQTile;
-  const int nq = nqt - qt0;  // >= 1 since k0 < L
-  const int n = p.group * nq;
+  const int n = p.group * (nqt - k0 / kQTile);  // steps: >= 1 since k0 < L
   const int64_t qstride = static_cast<int64_t>(p.hq) * D;
   const float* zero_f = reinterpret_cast<const float*>(g_zero_rows) + lane;
 
-  auto issue = [&](int it) {
-    const int head = kvh * p.group + it / nq;
-    const int q0 = (qt0 + it % nq) * kQTile;
-    __bf16* st = lds + (it & 1) * kStageElems;
-    const int pos = q0 + kRpw * wave;
+  // the tile that is loaded next: head ih of the group, query tile iq
+  int ih = 0, iq = nqt - 1;
+  auto issue = [&](int stage) {  // waves 4-7 only
+    const int head = kvh * p.group + ih;
+    const int q0 = iq * kQTile;
+    if (++ih == p.group) {
+      ih = 0;
+      --iq;
+    }
+    __bf16* st = lds + stage * kStageElems;
+    const int pos = q0 + kRpw * pair;
     const int64_t off = (static_cast<int64_t>(lo + pos) * p.hq + head) * D;
-    load_pair_async<D, kRpw>(st, p.q + off, p.dout + off, qstride, L - pos, wave, lane);
-    const float* plane = (wave & 1) ? p.ws_l2 : p.ws_d;
-    const int qq = q0 + lane;
-    const float* src = qq < L ? plane + static_cast<int64_t>(head) * p.total + lo + qq : zero_f;
-    dma_b32(src, __builtin_amdgcn_readfirstlane(lds_addr(st + 2 * BT::kElems + 128 * wave)));
+    load_pair_async<D, kRpw>(st, p.q + off, p.dout + off, qstride, L - pos, pair, lane);
+    if (pair < 2) {
+      const float* plane = pair == 0 ? p.ws_d : p.ws_l2;
+      const int qq = q0 + lane;
+      const float* src = qq < L ? plane + static_cast<int64_t>(head) * p.total + lo + qq : zero_f;
+      dma_b32(src, __builtin_amdgcn_readfirstlane(lds_addr(st + 2 * BT::kElems + 128 * pair)));
+    }
   };
 
-  f32x4 dv_acc[NDB][2], dk_acc[NDB][2];
+  f32x4 acc[NDB][2];  // dV^T, or dK^T in the late waves
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-      dv_acc[db][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-      dk_acc[db][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
+    for (int nb = 0; nb < 2; ++nb) acc[db][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 s[4][2];
+  bf16x8 wb[2][2];  // P, or dS, of the last tile in the products' operand order
   const float c = p.c;
+  const uint32_t lds0 = lds_addr(lds);
+  // the early waves contract dO with P and score Q; the late ones Q with dS and dO
+  const uint32_t tr_off = late ? 0 : BT::kElems * 2, row_off = late ? BT::kElems * 2 : 0;
 
-  issue(0);
-  // the K/V operands (and stage 0) have landed; the compiler's own wait, so
-  // that it does not keep those register loads pending into the loop, where
-  // its waits would also cover the next stage's loads
-  wait_vmem_below<0>();
-  auto step = [&](int it, auto stage_const) {  // step it, in stage SI = it % 2
-    constexpr int SI = decltype(stage_const)::value;
-    // stage it has landed in every wave, and every wave is done with stage it-1
-    wait_barrier<0>();
-    if (it + 1 < n) issue(it + 1);
-    const __bf16* qs = lds + SI * kStageElems;
-    const __bf16* dos = qs + BT::kElems;
-    const float* dvec = reinterpret_cast<const float*>(qs + 2 * BT::kElems);
-    const float* lvec = dvec + 64;
-    const int q0 = (qt0 + it % nq) * kQTile;
-
-    // S = Q K^T and dP = dO V^T: rows = queries 16*qb + 4*g + j, column = key 16*nb + col
-    f32x4 s[4][2], dp[4][2];
+  // weights of the tile in `stage` with its first query at q0
+  auto vector_phase = [&](int stage, int q0) {
+    const float* dvec = reinterpret_cast<const float*>(lds + stage * kStageElems + 2 * BT::kElems);
+    float w[2][4][4];
+    if (!late) {
+      const float* lvec = dvec + 64;
+      // P; keys after the query, and rows past the sequence, get P = 0
+      const bool full = (q0 >= kw0 + kKeysPerPair - 1) && (q0 + kQTile <= L);  // wave-uniform
+      auto weights = [&](auto masked) {
 #pragma unroll
-    for (int qb = 0; qb < 4; ++qb) {
-      bf16x8 a[NST], b[NST];
-      read_row_operand<D>(qs, qb, lane, a);
-      read_row_operand<D>(dos, qb, lane, b);
+        for (int qb = 0; qb < 4; ++qb) {
+          const f32x4 l2 = *reinterpret_cast<const f32x4*>(lvec + 16 * qb + 4 * g);
 #pragma unroll
-      for (int nb = 0; nb < 2; ++nb) {
-        f32x4 x = {0.f, 0.f, 0.f, 0.f}, y = {0.f, 0.f, 0.f, 0.f};
+          for (int nb = 0; nb < 2; ++nb) {
+            f32x4 pv;
 #pragma unroll
-        for (int st = 0; st < NST; ++st) x = mfma16(a[st], kf[nb][st], x);
-#pragma unroll
-        for (int st = 0; st < NST; ++st) y = mfma16(b[st], vf[nb][st], y);
-        s[qb][nb] = x;
-        dp[qb][nb] = y;
-      }
-    }
-
-    // P and dS = P (dP - D); keys after the query, and rows past the
-    // sequence, get P = 0
-    const bool full = (q0 >= kw0 + kKeysPerWave - 1) && (q0 + kQTile <= L);  // wave-uniform
-    float pv[2][4][4], dsv[2][4][4];
-    auto weights = [&](auto masked) {
+            for (int j = 0; j < 4; ++j) {
+              float x = hw_exp2(__builtin_fmaf(s[qb][nb][j], c, -l2[j]));
+              if constexpr (decltype(masked)::value) {
+                const int qp = q0 + 16 * qb + 4 * g + j;
+                const int kp = kw0 + 16 * nb + col;
+                x = (kp <= qp && qp < L) ? x : 0.f;
+              }
+              pv[j] = x;
+              w[nb][qb][j] = x;
+            }
+            pbuf[pair][2 * qb + nb][lane] = pv;
+          }
+        }
+      };
+      if (full)
+        weights(std::false_type{});
+      else
+        weights(std::true_type{});
+    } else {
+      // dS = P (dP - D)
 #pragma unroll
       for (int qb = 0; qb < 4; ++qb) {
-        const f32x4 l2 = *reinterpret_cast<const f32x4*>(lvec + 16 * qb + 4 * g);
         const f32x4 dd = *reinterpret_cast<const f32x4*>(dvec + 16 * qb + 4 * g);
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
+        for (int nb = 0; nb < 2; ++nb) {
+          const f32x4 pv = pbuf[pair][2 * qb + nb][lane];
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            float x = hw_exp2(__builtin_fmaf(s[qb][nb][j], c, -l2[j]));
-            if constexpr (decltype(masked)::value) {
-              const int qp = q0 + 16 * qb + 4 * g + j;
-              const int kp = kw0 + 16 * nb + col;
-              x = (kp <= qp && qp < L) ? x : 0.f;
-            }
-            pv[nb][qb][j] = x;
-            dsv[nb][qb][j] = x * (dp[qb][nb][j] - dd[j]);
-          }
+          for (int j = 0; j < 4; ++j) w[nb][qb][j] = pv[j] * (s[qb][nb][j] - dd[j]);
+        }
       }
-    };
-    if (full)
-      weights(std::false_type{});
-    else
-      weights(std::true_type{});
-    bf16x8 pb[2][2], sb[2][2];
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-      pack_rows(pv[nb], pb[nb]);
-      pack_rows(dsv[nb], sb[nb]);
     }
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) pack_rows(w[nb], wb[nb]);
+  };
 
-    // dV^T += dO^T P and dK^T += Q^T dS (contracting over the 64 queries)
-#pragma unroll
-    for (int db = 0; db < NDB; ++db) {
-      bf16x8 ot[2], qtr[2];
-      read_tr_operand<D>(dos, db, lane, ot);
-      read_tr_operand<D>(qs, db, lane, qtr);
-#pragma unroll
-      for (int nb = 0; nb < 2; ++nb) {
-#pragma unroll
-        for (int st = 0; st < 2; ++st) dv_acc[db][nb] = mfma16(ot[st], pb[nb][st], dv_acc[db][nb]);
-#pragma unroll
-        for (int st = 0; st < 2; ++st) dk_acc[db][nb] = mfma16(qtr[st], sb[nb][st], dk_acc[db][nb]);
+  if (late) {
+    issue(0);
+    if (n > 1) issue(1);
+  }
+  // the key operands (and stage 0) have landed; the compiler's own wait, so
+  // that it does not keep those register loads pending into the loop
+  wait_vmem_below<0>();
+  if (late) __builtin_amdgcn_s_barrier();  // the late waves' extra slot (nothing is pending here)
+
+  // step t: its tile in stage t % 3, the previous tile's in `prev`
+  int cur = 0, prev = 2, vh = 0, vq = nqt - 1;  // vh, vq: head and query tile of step t
+  auto step = [&](int t, auto prev_const, auto scores_const) {
+    constexpr bool kPrev = decltype(prev_const)::value, kScores = decltype(scores_const)::value;
+    __builtin_amdgcn_sched_barrier(0);
+    lds_barrier();
+    __builtin_amdgcn_s_setprio(2);
+    __builtin_amdgcn_sched_barrier(0);
+    const int next = cur == kStages - 1 ? 0 : cur + 1;
+    dkdv_matrix_phase<D, kPrev, kScores>(lds0 + prev * (kStageElems * 2) + tr_off,
+                                         lds0 + cur * (kStageElems * 2) + row_off, wb, xf, acc, s, lane);
+    if constexpr (kScores) {
+      __builtin_amdgcn_sched_barrier(0);
+      wait_vmem_below<0>();  // tile t+1, loaded a step ago (free in the early waves)
+      lds_barrier();
+      __builtin_amdgcn_s_setprio(0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (late && t + 2 < n) issue(prev);
+      vector_phase(cur, vq * kQTile);
+      if (++vh == p.group) {
+        vh = 0;
+        --vq;
       }
+      prev = cur;
+      cur = next;
     }
   };
-  // unrolled by the stage count: stage addresses are constant offsets
-  for (int it = 0; it < n; it += 2) {
-    step(it, std::integral_constant<int, 0>{});
-    if (it + 1 < n) step(it + 1, std::integral_constant<int, 1>{});
-  }
+  step(0, std::false_type{}, std::true_type{});
+#pragma unroll 1
+  for (int t = 1; t < n; ++t) step(t, std::true_type{}, std::true_type{});
+  step(n, std::true_type{}, std::false_type{});
+  if (!late) lds_barrier();  // the early waves' matching slot
 
   // lane (g, col): key kw0 + 16*nb + col, d = 16*db + 4*g .. +3
+  __bf16* dst = late ? p.dk : p.dv;
 #pragma unroll
   for (int nb = 0; nb < 2; ++nb) {
     const int kp = kw0 + 16 * nb + col;
@@ -371,14 +503,10 @@ __global__ __launch_bounds__(kKvWaves * 64, 1) void bwd_dkdv_kernel(BwdParams p)
       const int64_t off = (static_cast<int64_t>(lo + kp) * p.hkv + kvh) * D + 4 * g;
 #pragma unroll
       for (int db = 0; db < NDB; ++db) {
-        bf16x4 wk, wv;
+        bf16x4 o;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          wk[j] = to_bf16(dk_acc[db][nb][j] * p.scale);
-          wv[j] = to_bf16(dv_acc[db][nb][j]);
-        }
-        *reinterpret_cast<bf16x4*>(p.dk + off + 16 * db) = wk;
-        *reinterpret_cast<bf16x4*>(p.dv + off + 16 * db) = wv;
+        for (int j = 0; j < 4; ++j) o[j] = to_bf16(late ? acc[db][nb][j] * p.scale : acc[db][nb][j]);
+        *reinterpret_cast<bf16x4*>(dst + off + 16 * db) = o;
       }
     }
   }
@@ -391,6 +519,7 @@ constexpr int kDqWaves = 8;
 constexpr int kDqNB = 2;
 constexpr int kDqWaveRows = kDqNB * kQCols;
 constexpr int kDqRows = kDqWaves * kDqWaveRows;
+constexpr int kDqTileGroup = 2;  // query tiles (of all the group's heads) to a work unit, see xcd_unit
 
 template <int D>
 __global__ __launch_bounds__(kDqWaves * 64, 1) void bwd_dq_kernel(BwdParams p) {
@@ -400,11 +529,13 @@ __global__ __launch_bounds__(kDqWaves * 64, 1) void bwd_dq_kernel(BwdParams p) {
   constexpr int kStageElems = 2 * BT::kElems;  // K tile, V tile
   __shared__ __attribute__((aligned(1024))) __bf16 lds[2 * kStageElems];
 
-  const int per_qt = p.num_seqs * p.hq;
-  const int zrev = blockIdx.x / per_qt;  // query tiles counted from the end: longest work first
-  const int seq = (blockIdx.x % per_qt) / p.hq;
-  const int head = blockIdx.x % p.hq;
-  const int kvh = head / p.group;
+  const XcdUnit w = xcd_unit(blockIdx.x, kDqTileGroup * p.group);
+  if (w.unit >= p.dq_units) return;
+  // query tiles counted from the end: longest work first
+  const int zrev = w.unit / (p.num_seqs * p.hkv) * kDqTileGroup + w.member / p.group;
+  const int seq = (w.unit / p.hkv) % p.num_seqs;
+  const int kvh = w.unit % p.hkv;
+  const int head = kvh * p.group + w.member % p.group;
   int lo, L;
   seq_range(p, seq, lo, L);
   const int nqt = (L + kDqRows - 1) / kDqRows;
@@ -546,13 +677,20 @@ __global__ __launch_bounds__(kDqWaves * 64, 1) void bwd_dq_kernel(BwdParams p) {
 }
 
 template <int D>
-hipError_t launch_backward_d(const BwdParams& p, int max_seqlen, hipStream_t stream) {
-  const int64_t rows = static_cast<int64_t>(p.total) * p.hq;
+hipError_t launch_backward_d(const BwdParams& p0, int max_seqlen, hipStream_t stream) {
+  const int64_t rows = static_cast<int64_t>(p0.total) * p0.hq;
   constexpr int kPrepRows = 256 / (D / 8);
   const int64_t nprep = (rows + kPrepRows - 1) / kPrepRows;
-  const int64_t nkv = (static_cast<int64_t>(max_seqlen) + kKeyTile - 1) / kKeyTile * p.num_seqs * p.hkv;
-  const int64_t ndq = (static_cast<int64_t>(max_seqlen) + kDqRows - 1) / kDqRows * p.num_seqs * p.hq;
+  BwdParams p = p0;
+  const int64_t ktiles = (static_cast<int64_t>(max_seqlen) + kKeyTile - 1) / kKeyTile;
+  const int64_t kv_units = (ktiles + kKeyTileGroup - 1) / kKeyTileGroup * p.num_seqs * p.hkv;
+  const int64_t nkv = xcd_grid(kv_units, kKeyTileGroup);
+  const int64_t qtiles = (static_cast<int64_t>(max_seqlen) + kDqRows - 1) / kDqRows;
+  const int64_t dq_units = (qtiles + kDqTileGroup - 1) / kDqTileGroup * p.num_seqs * p.hkv;
+  const int64_t ndq = xcd_grid(dq_units, kDqTileGroup * p.group);
   if (nprep > 0x7FFFFFFF || nkv > 0x7FFFFFFF || ndq > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+  p.kv_units = static_cast<int>(kv_units);
+  p.dq_units = static_cast<int>(dq_units);
   hipLaunchKernelGGL(bwd_prep_kernel<D>, dim3(static_cast<unsigned>(nprep)), dim3(256), 0, stream, p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -60,7 +60,6 @@ struct PrefillParams {
 // that the G q heads of one (tile, sequence, kv head), which read the same K/V
 // tiles, run back to back on the same XCD, while work groups are spread over
 // XCDs in descending-cost order (query tiles counted from the end first).
-constexpr int kXcds = 8;
 
 // Byte offset, from the address of the wave's first row, of the 16-byte
 // piece this lane fetches in the first load instruction of a K (V) tile.

@@ -23,6 +23,20 @@
 
 namespace uattn {
 
+// The hardware deals consecutive workgroup ids to the 8 XCDs in turn, and each
+// XCD has its own L2.  Work is cut into units whose `members` workgroups read
+// the same tiles; unit u runs on XCD u % 8, its members back to back.
+constexpr int kXcds = 8;
+struct XcdUnit {
+  int unit, member;
+};
+__device__ __forceinline__ XcdUnit xcd_unit(int pid, int members) {
+  const int j = pid / kXcds;
+  return {j / members * kXcds + pid % kXcds, j % members};
+}
+// Workgroups of a launch over `units` units (ids past the last unit do nothing).
+inline int64_t xcd_grid(int64_t units, int64_t members) { return (units + kXcds - 1) / kXcds * kXcds * members; }
+
 // 256 zero bytes; the source of every tile row past the context.
 __device__ __attribute__((aligned(256))) uint4 g_zero_rows[16];
 

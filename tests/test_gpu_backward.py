@@ -87,6 +87,21 @@ def test_matches_oracle(ua, lens, hq, hkv, d, sigma):
         _check(name, gu.host_bits(got), r, s)
 
 
+# the dK/dV kernel's edges: a walk of one, two and three steps (its ring of three tiles), a sequence that ends a row
+# before, at and after a key tile (128) and a work unit (8 key tiles), kv head counts that do not divide the 8 XCDs
+TILE_EDGES = [
+    ([1, 63, 64, 65, 127, 128, 129], 2, 1, 128, 1.0),
+    ([1023, 1024, 1025], 3, 3, 64, 1.0),
+    ([1153, 5], 6, 2, 128, 0.5),
+    ([192], 5, 1, 64, 1.0),
+]
+
+
+@pytest.mark.parametrize("lens,hq,hkv,d,sigma", TILE_EDGES)
+def test_tile_edges_match_oracle(ua, lens, hq, hkv, d, sigma):
+    test_matches_oracle(ua, lens, hq, hkv, d, sigma)
+
+
 def test_repeated_calls_are_bitwise_equal(ua):
     q, k, v, do, cu = _inputs([700, 333, 64], 8, 2, 128, 1.0, 1)
     first = [gu.host_bits(x) for x in _run(ua, q, k, v, do, cu)]
