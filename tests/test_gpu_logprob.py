@@ -81,3 +81,26 @@ def test_logprob_constant_row(ua):
     tg = gu.dev_i32([0, 5, V - 1])
     got = ua.logprob(lg, tg).cpu().numpy()
     assert np.max(np.abs(got + np.log(V))) < 2e-6
+
+
+@pytest.mark.parametrize("V", [1, 7, 8, 8191, 8192, 8193, 40960, 40968, 81921])
+def test_logprob_vocab_edges(ua, V):
+    """Less than a vector, a vector per thread and one more, a thread's batch of five and one more, a ragged end; and a
+    row whose first 30 entries or all but the target are masked with -inf."""
+    import torch
+    T = 3
+    lg = inputs.logits_bf16(T, V, 2.0, tag=V)
+    tg = inputs.targets(T, V, tag=V)
+    tg[1:] = V - 1
+    lg[1, :min(30, V - 1)] = 0xFF80
+    lg[2, :V - 1] = 0xFF80
+    buf = np.zeros((T, (V + 7) // 8 * 8), dtype=np.uint16)
+    buf[:, :V] = lg
+    got = ua.logprob(gu.dev(buf)[:, :V], gu.dev_i32(tg)).cpu().numpy()
+    x = oracle.bf16_to_f64(lg)
+    m = x.max(axis=1)
+    ref = x[np.arange(T), tg] - m - np.log(np.exp(x - m[:, None]).sum(axis=1))
+    assert np.max(np.abs(got - ref)) < ATOL
+    # all but one masked: log of one weight exp2(fma(x, k, -fl(x k))), whose exponent is that product's rounding, at
+    # most 2^-24 |x k|
+    assert abs(got[2]) <= 2.0 ** -24 * abs(m[2]) + 2.0 ** -24
