@@ -306,7 +306,8 @@ size_t uattn_lm_head_logprob_workspace_bytes(int32_t num_rows, int32_t vocab);
  * epilogue reduces each row's logits of every 256-entry vocabulary tile to a
  * (max, sum of exp) pair in a fixed order (lanes, then the tile's four waves)
  * and picks out the target's logit; a second kernel folds each row's pairs in
- * ascending tile order.  The order depends only on vocabulary positions, so
+ * 16 runs of consecutive tiles, ascending inside a run and then run by run.
+ * The order depends only on vocabulary positions, so
  * a row's logp is bit-identical whatever num_rows or its place in the batch
  * (the reuse ratio of the two regimes is exactly 1).  It is not bit-identical
  * to uattn_logprob over the same logits, whose reduction is ordered

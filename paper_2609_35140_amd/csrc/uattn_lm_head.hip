@@ -2,12 +2,13 @@
 //
 // Each MFMA computes a 16 (vocab) x 16 (token) block of logits^T = W H^T, so
 // a lane's four results are four consecutive vocab entries of one token (one
-// 8-byte store).  Workgroup = 8 waves = 256 vocab rows x 256 tokens; wave
+// 8-byte store).  Workgroup = 8 waves = 256 vocab rows x 256 tokens (smaller
+// tiles for few tokens, see launch_rows); wave
 // (wm, wn) owns 64 vocab x 128 tokens (4 x 8 blocks), so each 16-byte LDS
 // operand read feeds 4 or 8 MFMAs.  K (the hidden dimension) is walked in
 // 64-wide chunks through a two-stage LDS ring filled by direct-to-LDS loads
-// (16-byte pieces XOR-swizzled by row, so the 16-lane operand reads hit
-// distinct banks), and every accumulator steps K in ascending 32-wide MFMA
+// (16-byte pieces XOR-swizzled by row, so the lanes of an operand read's
+// LDS cycle hit distinct banks), and every accumulator steps K in ascending 32-wide MFMA
 // steps from zero: a row's logits never depend on the batch, its size or the
 // row's place in a tile.
 //
@@ -30,7 +31,7 @@
 namespace uattn {
 namespace {
 
-constexpr int kKC = 64;       // hidden elements per chunk
+constexpr int kVocabTile = 256;  // vocab rows of a workgroup, and of a log-prob partial
 constexpr int kLmXcds = 8;
 
 struct LmHeadParams {
@@ -49,8 +50,11 @@ struct LmHeadParams {
 
 // VT vocab rows x TT tokens per workgroup, WM x WN waves (wave tile
 // VT/WM x TT/WN), a ring of STAGES chunks.
-template <int VT, int TT, int WM, int WN, int STAGES>
+template <int VT, int TT, int WM, int WN, int STAGES, int kKC>
 struct LmCfg {
+  static constexpr int kPieces = kKC / 8;  // 16-byte pieces of a row's chunk
+  // pieces are XOR-swizzled by row so that the lanes of an LDS cycle hit distinct banks
+  __device__ __forceinline__ static int swz(int row) { return row & (kPieces - 1) & 15; }
   static constexpr int NW = WM * WN;       // waves per workgroup
   static constexpr int BI = VT / WM / 16;   // 16-row vocab blocks per wave
   static constexpr int BJ = TT / WN / 16;   // 16-column token blocks per wave
@@ -64,9 +68,9 @@ struct LmCfg {
   };
 };
 
-template <int VT, int TT, int WM, int WN, int STAGES, bool kLogprob>
+template <int VT, int TT, int WM, int WN, int STAGES, int kKC, bool kLogprob>
 __global__ __launch_bounds__(WM * WN * 64, 1) void lm_head_kernel(LmHeadParams p) {
-  using C = LmCfg<VT, TT, WM, WN, STAGES>;
+  using C = LmCfg<VT, TT, WM, WN, STAGES, kKC>;
   constexpr int BI = C::BI, BJ = C::BJ;
   __shared__ __attribute__((aligned(1024))) typename C::Smem sm;
   const int pid = blockIdx.x;
@@ -88,14 +92,14 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void lm_head_kernel(LmHeadParams p
 #pragma unroll
     for (int i = 0; i < C::kAInstr; ++i) {
       const int slot = (wave * C::kAInstr + i) * 64 + lane;
-      const int row = slot >> 3, lp = (slot & 7) ^ (row & 7);
+      const int row = slot / C::kPieces, lp = (slot % C::kPieces) ^ C::swz(row);
       const __bf16* src = (v0 + row < p.V) ? p.w + static_cast<int64_t>(v0 + row) * p.ws + k0 + 8 * lp : zero;
       dma_b128(src, __builtin_amdgcn_readfirstlane(lds_addr(a + (wave * C::kAInstr + i) * 512)));
     }
 #pragma unroll
     for (int i = 0; i < C::kBInstr; ++i) {
       const int slot = (wave * C::kBInstr + i) * 64 + lane;
-      const int row = slot >> 3, lp = (slot & 7) ^ (row & 7);
+      const int row = slot / C::kPieces, lp = (slot % C::kPieces) ^ C::swz(row);
       const __bf16* src = (t0 + row < p.T) ? p.h + static_cast<int64_t>(t0 + row) * p.hs + k0 + 8 * lp : zero;
       dma_b128(src, __builtin_amdgcn_readfirstlane(lds_addr(b + (wave * C::kBInstr + i) * 512)));
     }
@@ -137,12 +141,12 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void lm_head_kernel(LmHeadParams p
 #pragma unroll
       for (int i = 0; i < BI; ++i) {
         const int row = (VT / WM) * wm + 16 * i + r16;
-        av[i] = *reinterpret_cast<const bf16x8*>(a + row * kKC + 8 * (lp ^ (row & 7)));
+        av[i] = *reinterpret_cast<const bf16x8*>(a + row * kKC + 8 * (lp ^ C::swz(row)));
       }
 #pragma unroll
       for (int j = 0; j < BJ; ++j) {
         const int row = (TT / WN) * wn + 16 * j + r16;
-        bv[j] = *reinterpret_cast<const bf16x8*>(b + row * kKC + 8 * (lp ^ (row & 7)));
+        bv[j] = *reinterpret_cast<const bf16x8*>(b + row * kKC + 8 * (lp ^ C::swz(row)));
       }
 #pragma unroll
       for (int i = 0; i < BI; ++i)
@@ -250,60 +254,103 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void lm_head_kernel(LmHeadParams p
   }
 }
 
-// Fold of a token's vocab-tile partials in ascending tile order, then
+// Fold of a token's vocab-tile partials, then
 //   logp = (x_y - M) * inv_temperature - log2(S) * ln 2
-// (S is the sum of exp2((x - M) * inv_temperature * log2 e)).  The partials
-// are loaded kFoldBatch tiles at a time ahead of their fold, so the fold's
-// sequential chain does not wait for one memory round trip per tile.
+// (S is the sum of exp2((x - M) * inv_temperature * log2 e)).  A token's tiles
+// are cut into kFoldSegs runs of consecutive tiles, one thread each, folded in
+// ascending order inside a run and then run by run: the order depends on the
+// tile count alone.  One thread per token walked 594 tiles in 37 dependent
+// round trips (90 us, whatever the number of tokens); a run of 38 takes three.
 constexpr int kFoldBatch = 16;
+constexpr int kFoldSegs = 16;
+constexpr int kFoldTokens = 256 / kFoldSegs;  // tokens per workgroup
 __global__ __launch_bounds__(256) void logprob_fold_kernel(const float* __restrict__ part_m,
                                                            const float* __restrict__ part_s,
                                                            const float* __restrict__ y_logit,
                                                            const int32_t* __restrict__ targets, int32_t T, int32_t V,
                                                            int32_t n_vt, float it, float k, float* __restrict__ logp) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  if (t >= T) return;
-  const int y = targets[t];
-  const float xy = (y >= 0 && y < V) ? y_logit[t] : 0.f;
+  __shared__ float2 run[kFoldSegs][kFoldTokens];
+  const int tok = threadIdx.x % kFoldTokens, seg = threadIdx.x / kFoldTokens;
+  const int t = blockIdx.x * kFoldTokens + tok;
+  const int len = (n_vt + kFoldSegs - 1) / kFoldSegs;
+  const int first = seg * len, last = min(first + len, n_vt);
   float M = 0.f, S = 0.f;
-  for (int v0 = 0; v0 < n_vt; v0 += kFoldBatch) {
-    float bm[kFoldBatch], bs[kFoldBatch];
+  auto fold = [&](float m, float s) {
+    const float mn = vmax(M, m);
+    const float mk = mn * k;
+    S = S * hw_exp2(M * k - mk) + s * hw_exp2(m * k - mk);
+    M = mn;
+  };
+  if (t < T) {
+    for (int v0 = first; v0 < last; v0 += kFoldBatch) {
+      float bm[kFoldBatch], bs[kFoldBatch];
 #pragma unroll
-    for (int i = 0; i < kFoldBatch; ++i) {
-      const int64_t vt = min(v0 + i, n_vt - 1);
-      bm[i] = part_m[vt * T + t];
-      bs[i] = part_s[vt * T + t];
-    }
+      for (int i = 0; i < kFoldBatch; ++i) {
+        const int64_t vt = min(v0 + i, n_vt - 1);
+        bm[i] = part_m[vt * T + t];
+        bs[i] = part_s[vt * T + t];
+      }
 #pragma unroll
-    for (int i = 0; i < kFoldBatch; ++i) {
-      const int vt = v0 + i;
-      if (vt >= n_vt) break;
-      if (vt == 0) {
-        M = bm[i];
-        S = bs[i];
-      } else {
-        const float mn = vmax(M, bm[i]);
-        const float mk = mn * k;
-        S = S * hw_exp2(M * k - mk) + bs[i] * hw_exp2(bm[i] * k - mk);
-        M = mn;
+      for (int i = 0; i < kFoldBatch; ++i) {
+        const int vt = v0 + i;
+        if (vt >= last) break;
+        if (vt == first) {
+          M = bm[i];
+          S = bs[i];
+        } else {
+          fold(bm[i], bs[i]);
+        }
       }
     }
   }
+  run[seg][tok] = float2{M, S};
+  __syncthreads();
+  if (seg != 0 || t >= T) return;
+  for (int i = 1; i < kFoldSegs && i * len < n_vt; ++i) fold(run[i][tok].x, run[i][tok].y);
+  const int y = targets[t];
+  const float xy = (y >= 0 && y < V) ? y_logit[t] : 0.f;
   logp[t] = (y < 0 || y >= V) ? __builtin_nanf("") : (xy - M) * it - hw_log2(S) * 0.69314718055994530942f;
 }
 
-template <int VT, int TT, int WM, int WN, int STAGES, bool kLogprob>
+template <int VT, int TT, int WM, int WN, int STAGES, int kKC, bool kLogprob>
 hipError_t launch_cfg(LmHeadParams p, hipStream_t stream) {
   p.n_vt = (p.V + VT - 1) / VT;
   p.n_tt = (p.T + TT - 1) / TT;
   const int64_t nblocks = static_cast<int64_t>((p.n_vt + kLmXcds - 1) / kLmXcds) * kLmXcds * p.n_tt;
   if (nblocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL((lm_head_kernel<VT, TT, WM, WN, STAGES, kLogprob>), dim3(static_cast<unsigned>(nblocks)),
+  hipLaunchKernelGGL((lm_head_kernel<VT, TT, WM, WN, STAGES, kKC, kLogprob>), dim3(static_cast<unsigned>(nblocks)),
                      dim3(WM * WN * 64), 0, stream, p);
   return hipGetLastError();
 }
 
-constexpr int kVocabTile = 256;
+// Tile shape by the number of rows.  Every shape adds the same products in the
+// same order to an accumulator, so a row has the same bits in all of them.
+//
+// Up to about 128 rows the product is bound by the stream of the weights
+// (1.24 GB for 151,936 x 4096: 190 us at the read ceiling), and a tile padded to
+// 256 tokens spends 345 us on it at 8 rows.  What the stream wants is bytes in
+// flight that a barrier does not drain, so two workgroups to a CU (80 KB of
+// LDS each), and long runs of a row per load: a power-of-two row length puts
+// the same chunk of all rows on few memory channels.  Measured at 8 rows,
+// 151,936 x 4096 (and with rows 128 bytes longer): 64 vocab rows x 256-wide
+// chunks 229 us (201), x 128 256 us (206) with 64 token columns; 256 vocab
+// rows x 64-wide chunks 266 us (254), x 128 285 us (229); deeper rings of one
+// workgroup to a CU 276-286 us; operands straight to registers, 16 waves to a
+// CU, 299 us (284).
+// The log-prob epilogue reduces 256 vocab entries in one workgroup, so its
+// shapes keep 256 rows.
+template <bool kLogprob>
+hipError_t launch_rows(const LmHeadParams& p, hipStream_t stream) {
+  if constexpr (kLogprob) {
+    if (p.T <= 64) return launch_cfg<kVocabTile, 64, 4, 2, 2, 64, true>(p, stream);
+  } else {
+    if (p.T <= 16 && p.K % 256 == 0) return launch_cfg<64, 16, 4, 1, 2, 256, false>(p, stream);
+    if (p.T <= 64 && p.K % 128 == 0) return launch_cfg<64, 64, 4, 1, 2, 128, false>(p, stream);
+    if (p.T <= 64) return launch_cfg<64, 64, 4, 1, 2, 64, false>(p, stream);
+  }
+  if (p.T <= 128) return launch_cfg<kVocabTile, 128, 4, 2, 2, 64, kLogprob>(p, stream);
+  return launch_cfg<kVocabTile, 256, 4, 2, 2, 64, kLogprob>(p, stream);
+}
 
 }  // namespace
 
@@ -321,7 +368,7 @@ hipError_t launch_lm_head(const LmHeadLaunch& a, hipStream_t stream) {
   p.targets = nullptr;
   p.part_m = p.part_s = p.y_logit = nullptr;
   p.k = 0.f;
-  return launch_cfg<kVocabTile, 256, 4, 2, 2, false>(p, stream);
+  return launch_rows<false>(p, stream);
 }
 
 size_t lm_head_logprob_ws_bytes(int64_t num_rows, int64_t vocab) {
@@ -348,9 +395,9 @@ hipError_t launch_lm_head_logprob(const LmHeadLaunch& a, const int32_t* targets,
   p.part_s = ws + n_vt * a.num_rows;
   p.y_logit = ws + 2 * n_vt * a.num_rows;
   p.k = static_cast<float>(static_cast<double>(inv_temperature) * 1.4426950408889634);
-  hipError_t e = launch_cfg<kVocabTile, 256, 4, 2, 2, true>(p, stream);
+  hipError_t e = launch_rows<true>(p, stream);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(logprob_fold_kernel, dim3((a.num_rows + 255) / 256), dim3(256), 0, stream, p.part_m, p.part_s,
+  hipLaunchKernelGGL(logprob_fold_kernel, dim3((a.num_rows + kFoldTokens - 1) / kFoldTokens), dim3(256), 0, stream, p.part_m, p.part_s,
                      p.y_logit, targets, a.num_rows, a.vocab, static_cast<int32_t>(n_vt), inv_temperature, p.k, logp);
   return hipGetLastError();
 }

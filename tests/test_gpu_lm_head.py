@@ -78,6 +78,37 @@ def test_fused_logprob_matches_oracle(ua, T, V, H, it):
     assert float((lp2.double() - two.double()).abs().max()) < 2e-5
 
 
+@pytest.mark.parametrize("V,H", [(255, 64), (257, 192), (321, 256), (1000, 640)])
+def test_tile_shapes_give_the_same_bits(ua, V, H):
+    """The tile shape follows the number of rows (16, 64 and 128 are its steps) and the width (chunks of 64, 128, 256):
+    rows of a small call equal the same rows of a large one, with and without stored logits."""
+    import torch
+    T = 300
+    h = gu.dev(inputs.normal_bf16((T, H), 1.0, 96, H))
+    w = gu.dev(inputs.normal_bf16((V, H), 0.25, 97, H))
+    tg = gu.dev_i32(inputs.targets(T, V, tag=H))
+    full, full_lp = ua.lm_head(h, w), ua.lm_head_logprob(h, w, tg)
+    for n in (1, 15, 16, 17, 63, 64, 65, 127, 128, 129):
+        part = ua.lm_head(h[:n], w)
+        assert torch.equal(part.view(torch.int16), full[:n].view(torch.int16)), n
+        stored = torch.empty((n, (V + 7) // 8 * 8), dtype=torch.bfloat16, device="cuda")[:, :V]
+        lp = ua.lm_head_logprob(h[:n], w, tg[:n], logits=stored)
+        assert torch.equal(lp.view(torch.int32), full_lp[:n].view(torch.int32)), n
+        assert torch.equal(stored.view(torch.int16), full[:n].view(torch.int16)), n
+
+
+@pytest.mark.parametrize("V", [200, 4096, 4097, 8193])
+def test_fused_logprob_fold_runs(ua, V):
+    """1, 16, 17 and 33 vocabulary tiles: runs of one, full and empty runs of the fold."""
+    T, H = 20, 64
+    h = inputs.normal_bf16((T, H), 1.0, 94, T, V)
+    w = inputs.normal_bf16((V, H), 0.25, 95, T, V)
+    tg = inputs.targets(T, V, tag=V)
+    lp = ua.lm_head_logprob(gu.dev(h), gu.dev(w), gu.dev_i32(tg)).cpu().numpy().astype(np.float64)
+    ref, bound = oracle.lm_head_logprob_fp64(h, w, tg, 1.0)
+    assert np.all(np.abs(lp - ref) <= bound)
+
+
 def test_fused_logprob_rows_are_batch_invariant(ua):
     import torch
     T, V, H = 640, 1500, 1024
