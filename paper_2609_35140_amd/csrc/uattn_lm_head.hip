@@ -24,6 +24,8 @@
 // each token's partials in ascending vocab-tile order.  Every reduction has
 // a structure fixed by vocab positions alone (lane, wave and tile order), so
 // a token's result does not depend on the batch or its place in it.
+#include <type_traits>
+
 #include "uattn_internal.h"
 #include "uattn_numerics.h"
 #include "uattn_tile_io.h"
@@ -68,17 +70,122 @@ struct LmCfg {
   };
 };
 
+// What becomes of a workgroup's accumulators: the bf16 logits (if p.out), and
+// the log-prob partials of its vocab tile.  `red`: LDS of the K loop.
+template <int VT, int TT, int WM, int WN, bool kLogprob>
+__device__ __forceinline__ void lm_head_epilogue(const LmHeadParams& p, const f32x4 (&acc)[VT / WM / 16][TT / WN / 16],
+                                                 float* red /* [WM][TT] per-wave maxima, then sums */,
+                                                 const int (&ytgt)[kLogprob ? TT / WN / 16 : 1], int v0, int t0, int vt,
+                                                 int tid) {
+  constexpr int BI = VT / WM / 16, BJ = TT / WN / 16;
+  const int lane = tid & 63, r16 = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave % WM, wn = wave / WM;
+  // lane: token 16j + r16 of the wave's columns, vocab 16i + 4g .. +3 of its rows
+  if (p.out != nullptr) {
+#pragma unroll
+    for (int j = 0; j < BJ; ++j) {
+      const int t = t0 + (TT / WN) * wn + 16 * j + r16;
+      if (t >= p.T) continue;
+      __bf16* orow = p.out + static_cast<int64_t>(t) * p.os;
+#pragma unroll
+      for (int i = 0; i < BI; ++i) {
+        const int v = v0 + (VT / WM) * wm + 16 * i + 4 * g;
+        bf16x4 o;
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) o[jj] = to_bf16(acc[i][j][jj]);
+        if (v + 3 < p.V) {
+          *reinterpret_cast<bf16x4*>(orow + v) = o;
+        } else {
+#pragma unroll
+          for (int jj = 0; jj < 4; ++jj)
+            if (v + jj < p.V) orow[v + jj] = o[jj];
+        }
+      }
+    }
+  }
+  if constexpr (kLogprob) {
+    static_assert(VT == 256 && WM == 4 && TT <= 256, "reduction layout: four waves of 64 vocab entries");
+    // the K loop's LDS is free once every wave is past its last chunk
+    lds_barrier();
+    const float k = p.k;
+    // x = the stored bf16 logit (raw; the temperature sits in k), -inf past the vocabulary
+    float x[BJ][BI][4];
+#pragma unroll
+    for (int j = 0; j < BJ; ++j) {
+      const int tl = (TT / WN) * wn + 16 * j + r16;
+      const int t = t0 + tl;
+      const int y = ytgt[j];
+#pragma unroll
+      for (int i = 0; i < BI; ++i) {
+        const int v = v0 + (VT / WM) * wm + 16 * i + 4 * g;
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+          const float xv = static_cast<float>(to_bf16(acc[i][j][jj]));
+          x[j][i][jj] = (v + jj < p.V) ? xv : neg_inf();
+          if (v + jj == y) p.y_logit[t] = xv;
+        }
+      }
+      // the wave's maximum over its 64 entries of this token (max is exact: any order)
+      float mx = neg_inf();
+#pragma unroll
+      for (int i = 0; i < BI; ++i) mx = vmax(vmax(mx, vmax(x[j][i][0], x[j][i][1])), vmax(x[j][i][2], x[j][i][3]));
+      mx = max_xor32(max_xor16(mx));
+      if (g == 0) red[wm * TT + tl] = mx;
+    }
+    lds_barrier();
+    float m_tile[BJ];
+#pragma unroll
+    for (int j = 0; j < BJ; ++j) {
+      const int tl = (TT / WN) * wn + 16 * j + r16;
+      m_tile[j] = vmax(vmax(red[tl], red[TT + tl]), vmax(red[2 * TT + tl], red[3 * TT + tl]));
+    }
+    lds_barrier();
+#pragma unroll
+    for (int j = 0; j < BJ; ++j) {
+      const int tl = (TT / WN) * wn + 16 * j + r16;
+      const float mk = m_tile[j] * k;
+      // fixed order: the four values of a block in pairs, then the blocks in pairs
+      float sb[BI];
+#pragma unroll
+      for (int i = 0; i < BI; ++i) {
+        float e[4];
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) e[jj] = hw_exp2(__builtin_fmaf(x[j][i][jj], k, -mk));
+        sb[i] = (e[0] + e[1]) + (e[2] + e[3]);
+      }
+      float sum = (sb[0] + sb[1]) + (sb[2] + sb[3]);
+      // the four lane groups of the column: the same pairs in every lane
+      sum = sum + __shfl_xor(sum, 16, 64);
+      sum = sum + __shfl_xor(sum, 32, 64);
+      if (g == 0) red[wm * TT + tl] = sum;
+    }
+    lds_barrier();
+    if (tid < TT) {
+      const int t = t0 + tid;
+      if (t < p.T) {
+        const float s4 = (red[tid] + red[TT + tid]) + (red[2 * TT + tid] + red[3 * TT + tid]);
+        p.part_s[static_cast<int64_t>(vt) * p.T + t] = s4;
+      }
+    }
+    // the tile maxima (the same value in every wave): lanes g == 0 of the waves wm == 0 write them
+    if (wm == 0 && g == 0) {
+#pragma unroll
+      for (int j = 0; j < BJ; ++j) {
+        const int t = t0 + (TT / WN) * wn + 16 * j + r16;
+        if (t < p.T) p.part_m[static_cast<int64_t>(vt) * p.T + t] = m_tile[j];
+      }
+    }
+  }
+}
+
+// One workgroup tile: vocab tile vt, tokens t0 .. t0 + TT - 1.
 template <int VT, int TT, int WM, int WN, int STAGES, int kKC, bool kLogprob>
-__global__ __launch_bounds__(WM * WN * 64, 1) void lm_head_kernel(LmHeadParams p) {
+__device__ __forceinline__ void lm_head_tile(const LmHeadParams& p, typename LmCfg<VT, TT, WM, WN, STAGES, kKC>::Smem& sm,
+                                             int vt, int t0) {
   using C = LmCfg<VT, TT, WM, WN, STAGES, kKC>;
   constexpr int BI = C::BI, BJ = C::BJ;
-  __shared__ __attribute__((aligned(1024))) typename C::Smem sm;
-  const int pid = blockIdx.x;
-  const int xcd = pid % kLmXcds, kk = pid / kLmXcds;
-  const int vt = xcd + kLmXcds * (kk / p.n_tt);
-  const int tt = kk % p.n_tt;
-  if (vt >= p.n_vt) return;
-  const int v0 = vt * VT, t0 = tt * TT;
+  const int v0 = vt * VT;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave % WM, wn = wave / WM;
@@ -155,103 +262,174 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void lm_head_kernel(LmHeadParams p
     }
   }
 
-  // lane: token 16j + r16 of the wave's columns, vocab 16i + 4g .. +3 of its rows
-  if (p.out != nullptr) {
-#pragma unroll
-    for (int j = 0; j < BJ; ++j) {
-      const int t = t0 + (TT / WN) * wn + 16 * j + r16;
-      if (t >= p.T) continue;
-      __bf16* orow = p.out + static_cast<int64_t>(t) * p.os;
-#pragma unroll
-      for (int i = 0; i < BI; ++i) {
-        const int v = v0 + (VT / WM) * wm + 16 * i + 4 * g;
-        bf16x4 o;
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) o[jj] = to_bf16(acc[i][j][jj]);
-        if (v + 3 < p.V) {
-          *reinterpret_cast<bf16x4*>(orow + v) = o;
-        } else {
-#pragma unroll
-          for (int jj = 0; jj < 4; ++jj)
-            if (v + jj < p.V) orow[v + jj] = o[jj];
-        }
-      }
-    }
+  lm_head_epilogue<VT, TT, WM, WN, kLogprob>(p, acc, reinterpret_cast<float*>(&sm), ytgt, v0, t0, vt, tid);
+}
+
+template <int VT, int TT, int WM, int WN, int STAGES, int kKC, bool kLogprob>
+__global__ __launch_bounds__(WM * WN * 64, 1) void lm_head_kernel(LmHeadParams p) {
+  __shared__ __attribute__((aligned(1024))) typename LmCfg<VT, TT, WM, WN, STAGES, kKC>::Smem sm;
+  const int pid = blockIdx.x;
+  const int xcd = pid % kLmXcds, kk = pid / kLmXcds;
+  const int vt = xcd + kLmXcds * (kk / p.n_tt);
+  const int tt = kk % p.n_tt;
+  if (vt >= p.n_vt) return;
+  lm_head_tile<VT, TT, WM, WN, STAGES, kKC, kLogprob>(p, sm, vt, tt * TT);
+}
+
+// The 256 x 256 tile of a large call, 8 waves of 64 vocab x 128 tokens, bound by
+// matrix issue.  Each wave holds the operands of two K steps of 32: while the
+// 32 products of one run, the LDS reads of the next go out between them, so no
+// product waits for LDS.  One barrier per 64-wide chunk, placed in the middle
+// of it: by then every wave has read the rest of the chunk into registers, so
+// its stage can be refilled at once (chunk c + 2, a whole chunk ahead of its
+// use) and every wave leaves the barrier with 32 products ready to issue.
+// The loads take a uniform base per matrix and one 32-bit offset per
+// instruction; rows past the vocabulary or the batch are clamped to the last
+// valid one (their results are not written).
+// 4100 x 151,936 x 4096 (5.1 TFLOP): 4.60 ms with a chunk's reads before its
+// products, 4.19 so, 4.05 with the last 4 tokens in a tile of 64 instead of 256
+// (1.26 PFLOP/s).  Matrix units busy 68% of the cycles at 1.78 GHz: the clock
+// falls as they get busier.  Half of the L2 requests miss, but blocks of 4 x 8,
+// 4 x 16 and 8 x 4 (vocab x token tiles) to an XCD instead of one vocab tile at
+// a time all take the same time.
+constexpr int kWideVT = kVocabTile, kWideTT = 256, kWideWM = 4, kWideWN = 2;
+constexpr int kWideKC = 64;
+constexpr int64_t kWideMaxStride = int64_t{1} << 22;  // 255 rows of it in a 32-bit byte offset
+
+template <bool kLogprob>
+__global__ __launch_bounds__(512, 1) void lm_head_wide_kernel(LmHeadParams p) {
+  constexpr int BI = kWideVT / kWideWM / 16, BJ = kWideTT / kWideWN / 16;  // 4 x 8 blocks of 16 x 16
+  constexpr int kStage = (kWideVT + kWideTT) * kWideKC;                  // elements: weight rows, then hidden rows
+  __shared__ __attribute__((aligned(1024))) __bf16 sm[2 * kStage];
+  const int xcd = blockIdx.x % kLmXcds, kk = blockIdx.x / kLmXcds;
+  const int vt = xcd + kLmXcds * (kk / p.n_tt);
+  const int tt = kk % p.n_tt;
+  if (vt >= p.n_vt) return;
+  const int v0 = vt * kWideVT, t0 = tt * kWideTT;
+  // a last tile of few tokens: not padded to 256
+  if (p.T - t0 <= 64) {
+    lm_head_tile<kWideVT, 64, 4, 2, 2, kWideKC, kLogprob>(
+        p, *reinterpret_cast<typename LmCfg<kWideVT, 64, 4, 2, 2, kWideKC>::Smem*>(sm), vt, t0);
+    return;
   }
+  if (p.T - t0 <= 128) {
+    lm_head_tile<kWideVT, 128, 4, 2, 2, kWideKC, kLogprob>(
+        p, *reinterpret_cast<typename LmCfg<kWideVT, 128, 4, 2, 2, kWideKC>::Smem*>(sm), vt, t0);
+    return;
+  }
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave % kWideWM, wn = wave / kWideWM;
+  const int r16 = lane & 15, g = lane >> 4;
+
+  // wave w loads rows 32w .. 32w + 31 of both matrices, 8 rows (1 KB) per
+  // instruction; lane piece p of row r holds logical piece p ^ (r & 7)
+  uint32_t aoff[4], boff[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int row = 32 * wave + 8 * i + (lane >> 3);
+    const int piece = (lane & 7) ^ (lane >> 3);
+    aoff[i] = static_cast<uint32_t>((min(row, p.V - 1 - v0) * p.ws + 8 * piece) * 2);
+    boff[i] = static_cast<uint32_t>((min(row, p.T - 1 - t0) * p.hs + 8 * piece) * 2);
+  }
+  const __bf16* abase = p.w + static_cast<int64_t>(v0) * p.ws;
+  const __bf16* bbase = p.h + static_cast<int64_t>(t0) * p.hs;
+  const uint32_t ld0 = __builtin_amdgcn_readfirstlane(lds_addr(sm)) + 4096 * wave;
+  auto issue = [&](int c, int i) {  // instruction i of chunk c
+    const uint32_t d = ld0 + (c & 1) * (kStage * 2);
+    if (i < 4)
+      dma_b128_based(abase + c * kWideKC, aoff[i], d + 1024 * i);
+    else
+      dma_b128_based(bbase + c * kWideKC, boff[i - 4], d + kWideVT * kWideKC * 2 + 1024 * (i - 4));
+  };
+
+  f32x4 acc[BI][BJ];
+#pragma unroll
+  for (int i = 0; i < BI; ++i)
+#pragma unroll
+    for (int j = 0; j < BJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  struct Operands {
+    bf16x8 a[BI], b[BJ];
+  };
+  // LDS address of this lane's operand rows, K step 0; step 1 is one XOR away
+  const uint32_t sw = 16 * (g ^ (r16 & 7));
+  const uint32_t ra = lds_addr(sm) + (64 * wm + r16) * (kWideKC * 2) + sw;
+  const uint32_t rb = lds_addr(sm) + (kWideVT + 128 * wn + r16) * (kWideKC * 2) + sw;
+  typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
+  auto read = [&](Operands& o, int c, int s, int i) {  // operand i of step s of chunk c
+    const uint32_t st = (c & 1) * (kStage * 2);
+    const uint32_t base = ((i < BI ? ra : rb) ^ (64u * s)) + st;
+    const lds_bf16x8* q = reinterpret_cast<const lds_bf16x8*>(static_cast<uintptr_t>(base));
+    if (i < BI)
+      o.a[i] = q[16 * i * kWideKC / 8];
+    else
+      o.b[i - BI] = q[16 * (i - BI) * kWideKC / 8];
+  };
+  int ytgt[kLogprob ? BJ : 1];
   if constexpr (kLogprob) {
-    static_assert(VT == 256 && WM == 4 && TT <= 256, "reduction layout: four waves of 64 vocab entries");
-    // the K loop's LDS is free once every wave is past its last chunk
-    lds_barrier();
-    float* red = reinterpret_cast<float*>(&sm);   // [WM][TT] per-wave maxima, then per-wave sums
-    const float k = p.k;
-    // x = the stored bf16 logit (raw; the temperature sits in k), -inf past the vocabulary
-    float x[BJ][BI][4];
 #pragma unroll
     for (int j = 0; j < BJ; ++j) {
-      const int tl = (TT / WN) * wn + 16 * j + r16;
-      const int t = t0 + tl;
-      const int y = ytgt[j];
-#pragma unroll
-      for (int i = 0; i < BI; ++i) {
-        const int v = v0 + (VT / WM) * wm + 16 * i + 4 * g;
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-          const float xv = static_cast<float>(to_bf16(acc[i][j][jj]));
-          x[j][i][jj] = (v + jj < p.V) ? xv : neg_inf();
-          if (v + jj == y) p.y_logit[t] = xv;
-        }
-      }
-      // the wave's maximum over its 64 entries of this token (max is exact: any order)
-      float mx = neg_inf();
-#pragma unroll
-      for (int i = 0; i < BI; ++i) mx = vmax(vmax(mx, vmax(x[j][i][0], x[j][i][1])), vmax(x[j][i][2], x[j][i][3]));
-      mx = max_xor32(max_xor16(mx));
-      if (g == 0) red[wm * TT + tl] = mx;
-    }
-    lds_barrier();
-    float m_tile[BJ];
-#pragma unroll
-    for (int j = 0; j < BJ; ++j) {
-      const int tl = (TT / WN) * wn + 16 * j + r16;
-      m_tile[j] = vmax(vmax(red[tl], red[TT + tl]), vmax(red[2 * TT + tl], red[3 * TT + tl]));
-    }
-    lds_barrier();
-#pragma unroll
-    for (int j = 0; j < BJ; ++j) {
-      const int tl = (TT / WN) * wn + 16 * j + r16;
-      const float mk = m_tile[j] * k;
-      // fixed order: the four values of a block in pairs, then the blocks in pairs
-      float sb[BI];
-#pragma unroll
-      for (int i = 0; i < BI; ++i) {
-        float e[4];
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) e[jj] = hw_exp2(__builtin_fmaf(x[j][i][jj], k, -mk));
-        sb[i] = (e[0] + e[1]) + (e[2] + e[3]);
-      }
-      float sum = (sb[0] + sb[1]) + (sb[2] + sb[3]);
-      // the four lane groups of the column: the same pairs in every lane
-      sum = sum + __shfl_xor(sum, 16, 64);
-      sum = sum + __shfl_xor(sum, 32, 64);
-      if (g == 0) red[wm * TT + tl] = sum;
-    }
-    lds_barrier();
-    if (tid < TT) {
-      const int t = t0 + tid;
-      if (t < p.T) {
-        const float s4 = (red[tid] + red[TT + tid]) + (red[2 * TT + tid] + red[3 * TT + tid]);
-        p.part_s[static_cast<int64_t>(vt) * p.T + t] = s4;
-      }
-    }
-    // the tile maxima (the same value in every wave): lanes g == 0 of the waves wm == 0 write them
-    if (wm == 0 && g == 0) {
-#pragma unroll
-      for (int j = 0; j < BJ; ++j) {
-        const int t = t0 + (TT / WN) * wn + 16 * j + r16;
-        if (t < p.T) p.part_m[static_cast<int64_t>(vt) * p.T + t] = m_tile[j];
-      }
+      const int t = t0 + 128 * wn + 16 * j + r16;
+      ytgt[j] = t < p.T ? p.targets[t] : -1;
     }
   }
+
+  const int nk = p.K / kWideKC;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) issue(0, i);
+  if (nk > 1) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) issue(1, i);
+  }
+  wait_vmem_below<0>();  // the compiler's own wait: the targets and both chunks have landed
+  lds_barrier();
+  Operands o0, o1;
+#pragma unroll
+  for (int i = 0; i < BI + BJ; ++i) read(o0, 0, 0, i);
+
+  // the 32 products of one K step; between them the next step's reads (kNext)
+  // and a chunk's loads (kLoad), in this order
+  auto products = [&](const Operands& o, Operands& nx, int c, int s, auto next_const, auto load_const) {
+    constexpr bool kNext = decltype(next_const)::value, kLoad = decltype(load_const)::value;
+#pragma unroll
+    for (int j = 0; j < BJ; ++j) {
+#pragma unroll
+      for (int i = 0; i < BI; ++i) acc[i][j] = mfma16(o.a[i], o.b[j], acc[i][j]);
+      if constexpr (kNext) {
+        if (2 * j < BI + BJ) {
+          read(nx, c, s, 2 * j);
+          read(nx, c, s, 2 * j + 1);
+        }
+      }
+      if constexpr (kLoad) issue(c + 1, j);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (kNext) {
+      // said here, where the last two groups have covered the reads: at the
+      // loop's head the compiler would wait for the reads it has just issued
+      if (s == 0) __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    }
+  };
+  auto chunk = [&](int c, auto next_const, auto load_const) {
+    products(o0, o1, c, 1, std::true_type{}, std::false_type{});
+    // chunk c + 1 has landed (the only one in flight), and every wave has read all of chunk c
+    if constexpr (decltype(next_const)::value) {
+      wait_barrier<0>();
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    products(o1, o0, c + 1, 0, next_const, load_const);
+  };
+  int c = 0;
+#pragma unroll 1
+  for (; c + 2 < nk; ++c) chunk(c, std::true_type{}, std::true_type{});
+  if (c + 1 < nk) {
+    chunk(c, std::true_type{}, std::false_type{});
+    ++c;
+  }
+  chunk(c, std::false_type{}, std::false_type{});
+
+  lm_head_epilogue<kWideVT, kWideTT, kWideWM, kWideWN, kLogprob>(p, acc, reinterpret_cast<float*>(sm), ytgt, v0, t0, vt,
+                                                                 tid);
 }
 
 // Fold of a token's vocab-tile partials, then
@@ -323,6 +501,16 @@ hipError_t launch_cfg(LmHeadParams p, hipStream_t stream) {
   return hipGetLastError();
 }
 
+template <bool kLogprob>
+hipError_t launch_wide(LmHeadParams p, hipStream_t stream) {
+  p.n_vt = (p.V + kWideVT - 1) / kWideVT;
+  p.n_tt = (p.T + kWideTT - 1) / kWideTT;
+  const int64_t nblocks = static_cast<int64_t>((p.n_vt + kLmXcds - 1) / kLmXcds) * kLmXcds * p.n_tt;
+  if (nblocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+  hipLaunchKernelGGL(lm_head_wide_kernel<kLogprob>, dim3(static_cast<unsigned>(nblocks)), dim3(512), 0, stream, p);
+  return hipGetLastError();
+}
+
 // Tile shape by the number of rows.  Every shape adds the same products in the
 // same order to an accumulator, so a row has the same bits in all of them.
 //
@@ -348,8 +536,9 @@ hipError_t launch_rows(const LmHeadParams& p, hipStream_t stream) {
     if (p.T <= 64 && p.K % 128 == 0) return launch_cfg<64, 64, 4, 1, 2, 128, false>(p, stream);
     if (p.T <= 64) return launch_cfg<64, 64, 4, 1, 2, 64, false>(p, stream);
   }
-  if (p.T <= 128) return launch_cfg<kVocabTile, 128, 4, 2, 2, 64, kLogprob>(p, stream);
-  return launch_cfg<kVocabTile, 256, 4, 2, 2, 64, kLogprob>(p, stream);
+  if (p.T <= 128 || p.ws > kWideMaxStride || p.hs > kWideMaxStride)
+    return launch_cfg<kVocabTile, 128, 4, 2, 2, 64, kLogprob>(p, stream);
+  return launch_wide<kLogprob>(p, stream);
 }
 
 }  // namespace

@@ -80,15 +80,16 @@ def test_fused_logprob_matches_oracle(ua, T, V, H, it):
 
 @pytest.mark.parametrize("V,H", [(255, 64), (257, 192), (321, 256), (1000, 640)])
 def test_tile_shapes_give_the_same_bits(ua, V, H):
-    """The tile shape follows the number of rows (16, 64 and 128 are its steps) and the width (chunks of 64, 128, 256):
-    rows of a small call equal the same rows of a large one, with and without stored logits."""
+    """The tile shape follows the number of rows (16, 64 and 128 are its steps, of a call and of its last tile of 256) and
+    the width (chunks of 64, 128, 256): rows of a small call equal the same rows of a large one, with and without stored
+    logits."""
     import torch
-    T = 300
+    T = 700
     h = gu.dev(inputs.normal_bf16((T, H), 1.0, 96, H))
     w = gu.dev(inputs.normal_bf16((V, H), 0.25, 97, H))
     tg = gu.dev_i32(inputs.targets(T, V, tag=H))
     full, full_lp = ua.lm_head(h, w), ua.lm_head_logprob(h, w, tg)
-    for n in (1, 15, 16, 17, 63, 64, 65, 127, 128, 129):
+    for n in (1, 15, 16, 17, 63, 64, 65, 127, 128, 129, 256, 257, 320, 321, 384, 385, 513):
         part = ua.lm_head(h[:n], w)
         assert torch.equal(part.view(torch.int16), full[:n].view(torch.int16)), n
         stored = torch.empty((n, (V + 7) // 8 * 8), dtype=torch.bfloat16, device="cuda")[:, :V]
