@@ -331,6 +331,7 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(DecodeParams p) {
 
 constexpr int64_t kLdsBytesPerCu = 160 * 1024;
 constexpr int kLenScanMax = 4096;  // batches up to this size skip chunks past their longest entry
+constexpr int kListMax = 1024;     // and up to this size every empty chunk
 
 // Buffered variant, for long walks: finished partials wait in LDS and go to
 // the workspace in one burst per drain, instead of a few stores per item mixed
@@ -348,7 +349,8 @@ struct DecodeSmem {
   float tmax[kTilesPerChunk][NB][kQCols];      // column maxima of tile t's scores
   int32_t pend[kMaxPend][3];                   // (b * Hkv + kv head, chunk count, chunk)
   int32_t flag[kMaxPend];
-  int32_t lenmax[4];                           // per wave: the longest entry it read
+  int32_t lenmax[4];                           // per wave: the longest entry it read, or its entries' chunks
+  int32_t first[kListMax + 1];                 // chunks of the entries before each entry
   // kBuf: per pending item, G rows of D + 4 floats (acc; the padding spreads
   // the 16 heads of a store over the banks), then G (m, l) pairs
   alignas(16) float pbuf[kBuf ? kBufFloats : 4];
@@ -384,22 +386,78 @@ __global__ __launch_bounds__(256, kBuf ? 1 : 2) void decode_kernel(DecodeParams 
   const float c = p.c;
   const __bf16* zero = reinterpret_cast<const __bf16*>(g_zero_rows);
 
-  // Chunks past the longest entry hold no work.  When this workgroup's walk
-  // is longer than two items, read the batch's lengths first and stop the
-  // walk after the last chunk any entry has, so that a max_seqlen far above
-  // the actual lengths costs no round trips for empty items.
+  // Which item is which.  A short walk takes the items chunk-major over the
+  // full grid of max_seqlen's chunks, the empty ones among them.  When this
+  // workgroup's walk is longer than two items, it reads the batch's lengths
+  // first and walks only chunks that hold keys, entry by entry: an empty item
+  // costs most of a round trip, and in a ragged batch about half are empty
+  // (64 entries of 1280-16384 keys, 32/8 heads, the whole layer's step: 597 us
+  // with them in the walk, 426 without).
+  // kListMax bounds the LDS for the entries' first chunks; larger batches only
+  // drop the chunks past the longest entry.
   int ncand = ncand_all;
+  bool listed = false;
+  int lane_end = 0;   // listed: chunks of the entries before (lane + 1) * span
+  int span = 1;       // entries to a lane
   if (p.nchunk_max > 1 && p.batch <= kLenScanMax && ncand_all > 2 * stride) {
-    int lmax = 0;
-    for (int i = tid; i < p.batch; i += 256) lmax = max(lmax, p.seqlens[i]);
+    listed = p.batch <= kListMax;
+    int mine = 0, lmax = 0;
+    constexpr int kPer = kListMax / 256;
+    if (listed) {
+      int part[kPer];
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) lmax = max(lmax, __shfl_xor(lmax, m));
-    if (lane == 0) sm.lenmax[wave] = lmax;
-    __syncthreads();
-    lmax = max(max(sm.lenmax[0], sm.lenmax[1]), max(sm.lenmax[2], sm.lenmax[3]));
-    const int nch = min(max((min(lmax, p.max_seqlen) + kChunkKeys - 1) / kChunkKeys, 1), p.nchunk_max);
-    ncand = __builtin_amdgcn_readfirstlane(per_chunk * nch);
+      for (int i = 0; i < kPer; ++i) {
+        const int e = kPer * tid + i;
+        const int n = e < p.batch ? min(p.seqlens[e], p.max_seqlen) : 0;
+        part[i] = mine;
+        mine += n > 0 ? (n + kChunkKeys - 1) / kChunkKeys : 0;
+      }
+      int incl = mine;
+#pragma unroll
+      for (int sh = 1; sh < 64; sh <<= 1) {
+        const int o = __shfl_up(incl, sh, 64);
+        if (lane >= sh) incl += o;
+      }
+      if (lane == 63) sm.lenmax[wave] = incl;
+      __syncthreads();
+      int before = incl - mine;
+#pragma unroll
+      for (int w = 0; w < 4; ++w)
+        if (w < wave) before += sm.lenmax[w];
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) sm.first[kPer * tid + i] = before + part[i];
+      if (tid == 255) sm.first[kListMax] = before + mine;
+      __syncthreads();
+      span = (p.batch + 63) / 64;
+      lane_end = sm.first[min((lane + 1) * span, kListMax)];
+      ncand = __builtin_amdgcn_readfirstlane(sm.first[kListMax]) * p.hkv;
+    } else {
+      for (int i = tid; i < p.batch; i += 256) lmax = max(lmax, p.seqlens[i]);
+#pragma unroll
+      for (int m = 32; m >= 1; m >>= 1) lmax = max(lmax, __shfl_xor(lmax, m));
+      if (lane == 0) sm.lenmax[wave] = lmax;
+      __syncthreads();
+      lmax = max(max(sm.lenmax[0], sm.lenmax[1]), max(sm.lenmax[2], sm.lenmax[3]));
+      const int nch = min(max((min(lmax, p.max_seqlen) + kChunkKeys - 1) / kChunkKeys, 1), p.nchunk_max);
+      ncand = __builtin_amdgcn_readfirstlane(per_chunk * nch);
+    }
   }
+  // (chunk, entry, kv head) of item `it`, wave-uniform
+  struct Where {
+    int chunk, b, kvh;
+  };
+  auto locate = [&](int it) -> Where {
+    if (!listed) return {it / per_chunk, (it % per_chunk) / p.hkv, it % p.hkv};
+    const int u = it / p.hkv;  // position in the list of chunks
+    // the entry is the last whose first chunk is not after u: the lane whose
+    // entries contain it, then the entry among the lane's
+    int b = min(__builtin_popcountll(__builtin_amdgcn_ballot_w64(lane_end <= u)) * span, p.batch - 1);
+    if (span > 1) {
+      const int end = sm.first[min(b + lane + 1, kListMax)];
+      b = min(b + __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < span && end <= u)), p.batch - 1);
+    }
+    return {u - __builtin_amdgcn_readfirstlane(sm.first[b]), b, it % p.hkv};
+  };
 
   // An item's descriptor, for this wave: the entry length and the page of
   // each 16-key block of the wave's tile (table index clamped, so
@@ -407,26 +465,27 @@ __global__ __launch_bounds__(256, kBuf ? 1 : 2) void decode_kernel(DecodeParams 
   // scalar loads, counted apart from the vector loads and stores; the next
   // item's are issued before the current item's operand loads.
   struct Desc {
+    Where at;
     int len;
     int page[kKeyBlocks];
   };
   auto load_desc = [&](int it) -> Desc {
     Desc d;
-    const int chunk = it / per_chunk, b = (it % per_chunk) / p.hkv;
-    const int32_t* row = block_table + static_cast<int64_t>(b) * p.maxp;
-    d.len = seqlens[b];
+    d.at = locate(min(it, max(ncand, 1) - 1));
+    const int32_t* row = block_table + static_cast<int64_t>(d.at.b) * p.maxp;
+    d.len = it < ncand ? seqlens[d.at.b] : 0;
 #pragma unroll
     for (int kb = 0; kb < kKeyBlocks; ++kb) {
-      const int pos = (chunk * kTilesPerChunk + wave) * kTileKeys + 16 * kb;
+      const int pos = (d.at.chunk * kTilesPerChunk + wave) * kTileKeys + 16 * kb;
       d.page[kb] = row[min(pos >> p.page_shift, p.maxp - 1)];
     }
     return d;
   };
   auto make_item = [&](int it, const Desc& desc) -> Item {
     Item r;
-    r.chunk = it / per_chunk;
-    r.b = (it % per_chunk) / p.hkv;
-    r.kvh = it % p.hkv;
+    r.chunk = desc.at.chunk;
+    r.b = desc.at.b;
+    r.kvh = desc.at.kvh;
     r.n = it < ncand ? min(desc.len, p.max_seqlen) : 0;
     r.nch = (r.n + kChunkKeys - 1) / kChunkKeys;
     r.ntiles = (r.n >= 1 && r.chunk < r.nch) ? min(kTilesPerChunk, (r.n - 1) / kTileKeys - r.chunk * kTilesPerChunk + 1) : 0;
@@ -548,13 +607,13 @@ __global__ __launch_bounds__(256, kBuf ? 1 : 2) void decode_kernel(DecodeParams 
   // and PV phases.
   Desc desc = load_desc(blockIdx.x);
   Item cur = make_item(blockIdx.x, desc);
-  Desc desc_next = load_desc(min(blockIdx.x + stride, ncand_all - 1));
+  Desc desc_next = load_desc(blockIdx.x + stride);
   Operands op;
   issue_ops(cur, desc, op);
 #pragma unroll 1
   for (int item = blockIdx.x; item < ncand; item += stride) {
     const Item next = make_item(item + stride, desc_next);   // empty past the walk
-    const Desc desc_after = load_desc(min(item + 2 * stride, ncand_all - 1));
+    const Desc desc_after = load_desc(item + 2 * stride);
     const int tile = cur.chunk * kTilesPerChunk + wave;  // this wave's tile (sequence-relative)
     const bool tile_on = wave < cur.ntiles;
 

@@ -362,3 +362,37 @@ def test_oversized_max_seqlen_gives_the_same_bits(ua):
     assert torch.equal(big_lse.view(torch.int32), tight_lse.view(torch.int32))
     assert torch.equal(big.view(torch.int16), out[ti].view(torch.int16))
     assert torch.equal(big_lse.view(torch.int32), lse[ti].view(torch.int32))
+
+
+@pytest.mark.parametrize("batch,hkv,group,d,longest", [(63, 8, 1, 64, 1024), (64, 8, 5, 128, 1030), (65, 8, 2, 64, 1024),
+                                                       (130, 4, 17, 128, 900), (300, 8, 4, 64, 1500),
+                                                       (1024, 2, 1, 64, 700), (1025, 2, 1, 64, 700)])
+def test_ragged_decode_walk_lists_every_chunk(ua, batch, hkv, group, d, longest):
+    """Long walks over ragged batches (with empty entries) list the chunks that hold keys, one or several entries to a
+    lane, up to 1024 entries: every entry's output and lse equal those of short calls of 8 entries, empty ones stay
+    unwritten."""
+    import torch
+    page = 64
+    hq = hkv * group
+    lens = inputs.rng(71, batch, longest).integers(0, longest, size=batch, endpoint=True)
+    lens[inputs.rng(72, batch).integers(0, batch, size=max(1, batch // 10))] = 0
+    lens[0], lens[-1] = (0, longest) if batch % 2 else (longest, 0)
+    maxp = (longest + page - 1) // page
+    pages = 97                                        # entries share pages of a small pool
+    table = gu.dev_i32(inputs.rng(73, batch).integers(0, pages, size=(batch, maxp)))
+    q = inputs.normal_bf16_device((batch, hq, d), 1.0, 74, batch)
+    kp = inputs.normal_bf16_device((pages, hkv, page, d), 1.0, 75, batch)
+    vp = inputs.normal_bf16_device((pages, hkv, page, d), 1.0, 76, batch)
+    sl = gu.dev_i32(lens)
+    out = torch.full_like(q, 7.0)
+    lse = torch.full((batch, hq), 7.0, dtype=torch.float32, device="cuda")
+    ua.decode(q, kp, vp, table, sl, longest, out=out, lse=lse)
+    for i in range(0, batch, 8):
+        j = min(batch, i + 8)
+        o, e = torch.full_like(q[i:j], 7.0), torch.full_like(lse[i:j], 7.0)
+        ua.decode(q[i:j].contiguous(), kp, vp, table[i:j].contiguous(), sl[i:j].contiguous(), longest, out=o, lse=e)
+        assert torch.equal(o.view(torch.int16), out[i:j].view(torch.int16)), i
+        assert torch.equal(e.view(torch.int32), lse[i:j].view(torch.int32)), i
+    none = torch.from_numpy(lens == 0).cuda()
+    assert bool((out[none] == 7.0).all()) and bool((lse[none] == 7.0).all())
+    assert bool(torch.isfinite(out.float()).all()) and bool(torch.isfinite(lse).all())
