@@ -409,6 +409,207 @@ __global__ __launch_bounds__(kWaves * 64, 1) void prefill_kernel(PrefillParams p
   }
 }
 
+// ---------------------------------------------------------------------------
+// Short calls.  prefill_kernel's workgroups are 256 rows that walk their keys one
+// tile after the other, so a call of few rows leaves most of the GPU idle
+// behind chains of up to L/64 tiles.  Here a workgroup takes 128 rows and two
+// chunks at once: waves 0-3 (32 rows each) walk chunk 2r while waves 4-7 walk
+// chunk 2r + 1 for the same rows, each stream with its own K/V tiles (two
+// stages), and the two partials are folded in chunk order at the end of round
+// r.  For the fold a wave keeps half of d: it hands the other half of its
+// partial to its partner through the stage that the round's last tiles have
+// left.  Every row sees the operations of prefill_kernel in the same order.
+// ---------------------------------------------------------------------------
+constexpr int kSplitRowGroups = 4;
+constexpr int kSplitRows = kSplitRowGroups * kWaveRows;
+
+static_assert(2 * kSplitRowGroups == kWaves, "both kernels launch the same block");
+
+template <int D>
+__global__ __launch_bounds__(kWaves * 64, 1) void prefill_split_kernel(PrefillParams p) {
+  constexpr int NDB = D / 16, NDH = NDB / 2;
+  using TL = TileLayout<D>;
+  // [stage][stream], each a K and a V tile
+  __shared__ __attribute__((aligned(1024))) __bf16 lds[4 * TL::kStageElems];
+  __shared__ float2 part_ml[2][kSplitRowGroups][kNB][kQCols];
+  static_assert(kSplitRowGroups * kNB * NDH * 64 * 16 <= TL::kStageElems * 2, "a stream's half partials fit its stage");
+
+  const XcdUnit unit = xcd_unit(blockIdx.x, p.group);
+  if (unit.unit >= p.ngroups) return;
+  const int zrev = unit.unit / (p.num_seqs * p.hkv);
+  const int seq = (unit.unit / p.hkv) % p.num_seqs;
+  const int kvh = unit.unit % p.hkv;
+  const int head = kvh * p.group + unit.member;
+  const int lo = min(max(p.cu[seq], 0), p.total);
+  const int L = max(min(p.cu[seq + 1], p.total) - lo, 0);
+  const int qt = (L + kSplitRows - 1) / kSplitRows - 1 - zrev;
+  if (qt < 0) return;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rg = wave & 3, stream = wave >> 2;
+  const int g = lane >> 4, col = lane & 15;
+  const int q0 = qt * kSplitRows + kWaveRows * rg;
+  const bool wave_on = q0 < L;
+  const int last_tile = min(qt * kSplitRows + kSplitRows - 1, L - 1) / kTileKeys;  // of the workgroup
+  const int my_last_tile = q0 / kTileKeys;
+  const int nchunks = last_tile / kTilesPerChunk + 1;
+  const int nrounds = (nchunks + 1) / 2;
+  // steps of the last round: all of them unless its second chunk does not exist
+  const int last_steps = nchunks % 2 == 0 ? kTilesPerChunk : last_tile - (nchunks - 1) * kTilesPerChunk + 1;
+  const int nsteps = (nrounds - 1) * kTilesPerChunk + last_steps;
+
+  bf16x8 qf[kNB][D / 32];
+#pragma unroll
+  for (int nb = 0; nb < kNB; ++nb) {
+    const int qp = q0 + kQCols * nb + col;
+    if (wave_on && qp < L) {
+      const __bf16* qrow = p.q + (static_cast<int64_t>(lo + qp) * p.hq + head) * D + 8 * g;
+#pragma unroll
+      for (int st = 0; st < D / 32; ++st) qf[nb][st] = *reinterpret_cast<const bf16x8*>(qrow + 32 * st);
+    } else {
+#pragma unroll
+      for (int st = 0; st < D / 32; ++st)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) qf[nb][st][e] = static_cast<__bf16>(0.0f);
+    }
+  }
+
+  const int64_t row_stride = static_cast<int64_t>(p.hkv) * D;
+  // this stream's tile of step u
+  auto tile_of = [&](int u) { return (u / kTilesPerChunk * 2 + stream) * kTilesPerChunk + u % kTilesPerChunk; };
+  auto issue = [&](int u) {
+    const int t = tile_of(u);
+    if (t > last_tile) return;
+    const int pos = t * kTileKeys + 16 * rg;
+    const int64_t off = (static_cast<int64_t>(lo + pos) * p.hkv + kvh) * D;
+    load_tile_rows_async<D, 16>(lds + (2 * (u & 1) + stream) * TL::kStageElems, p.k + off, p.v + off, row_stride, L - pos, rg, lane);
+  };
+
+  f32x4 acc[kNB][NDB], A[kNB][NDH], lsum[kNB];
+  float m[kNB], M[kNB], Ls[kNB];
+  const float c = p.c;
+#pragma unroll
+  for (int nb = 0; nb < kNB; ++nb) {
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) acc[nb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int db = 0; db < NDH; ++db) A[nb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    lsum[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    m[nb] = M[nb] = neg_inf();
+    Ls[nb] = 0.f;
+  }
+
+  issue(0);
+  wait_vmem_below<0>();  // the query operands (and step 0's tiles); the compiler's own wait
+  auto step = [&](int u, auto first_const) {
+    constexpr bool kFirst = decltype(first_const)::value;
+    wait_barrier<0>();  // step u's tiles have landed in every wave; step u-1's stage has no readers left
+    if (u + 1 < nsteps) issue(u + 1);
+    const int t = tile_of(u);
+    if (wave_on && t <= my_last_tile) {
+      const __bf16* stage = lds + (2 * (u & 1) + stream) * TL::kStageElems;
+      f32x4 s[kNB][4];
+      bf16x8 pb[kNB][2];
+      float alpha[kNB];
+      qk_scores<D, kNB>(stage, qf, s, lane);
+#pragma unroll
+      for (int nb = 0; nb < kNB; ++nb) {
+        if (t == my_last_tile) mask_scores(s[nb], t * kTileKeys, q0 + kQCols * nb + col, lane);
+        if constexpr (kFirst) m[nb] = neg_inf();
+        alpha[nb] = softmax_tile(s[nb], m[nb], c);
+        pack_p(s[nb], pb[nb]);
+      }
+      pv_tile<D, kNB, NDB, kFirst>(stage + TL::kTileElems, pb, acc, lsum, alpha, 0, lane);
+    }
+  };
+
+  for (int r = 0; r < nrounds; ++r) {
+    const int u0 = r * kTilesPerChunk;
+    const int n = r + 1 < nrounds ? kTilesPerChunk : last_steps;
+    step(u0, std::true_type{});
+#pragma unroll 1
+    for (int i = 1; i < n; ++i) step(u0 + i, std::false_type{});
+    // ---- the fold of chunks 2r and 2r + 1: this wave's half of d
+    const bool two = 2 * r + 1 < nchunks;
+    __bf16* stage = lds + 2 * ((u0 + n - 1) & 1) * TL::kStageElems;
+    lds_barrier();  // the round's last tiles have no readers left
+    // compiled for each stream, so that the accumulators are indexed by constants
+    auto give = [&](auto stream_const) {
+      constexpr int kS = decltype(stream_const)::value;
+      f32x4* mine = reinterpret_cast<f32x4*>(stage + kS * TL::kStageElems) + rg * (kNB * NDH * 64) + lane;
+#pragma unroll
+      for (int nb = 0; nb < kNB; ++nb) {
+#pragma unroll
+        for (int db = 0; db < NDH; ++db) mine[(nb * NDH + db) * 64] = acc[nb][kS == 0 ? NDH + db : db];
+        if (g == 0) part_ml[kS][rg][nb][col] = float2{m[nb], lsum[nb][0]};
+      }
+    };
+    if (stream == 0)
+      give(std::integral_constant<int, 0>{});
+    else if (two)
+      give(std::integral_constant<int, 1>{});
+    lds_barrier();
+    auto fold_round = [&](auto stream_const) {
+      constexpr int kS = decltype(stream_const)::value;
+      const f32x4* other = reinterpret_cast<const f32x4*>(stage + (1 - kS) * TL::kStageElems) + rg * (kNB * NDH * 64) + lane;
+      auto fold_chunk = [&](auto chunk_const) {
+        constexpr int kC = decltype(chunk_const)::value;
+#pragma unroll
+        for (int nb = 0; nb < kNB; ++nb) {
+          const float2 ml = part_ml[kC][rg][nb][col];
+          f32x4 x[NDH];
+#pragma unroll
+          for (int db = 0; db < NDH; ++db)
+            if constexpr (kC == kS)
+              x[db] = acc[nb][kS == 0 ? db : NDH + db];
+            else
+              x[db] = other[(nb * NDH + db) * 64];
+          if (kC == 0 && r == 0) {
+            M[nb] = ml.x;
+            Ls[nb] = ml.y;
+#pragma unroll
+            for (int db = 0; db < NDH; ++db) A[nb][db] = x[db];
+          } else {
+            const FoldScale f = fold_scale(M[nb], ml.x, c);
+            Ls[nb] = fold_val(f, Ls[nb], ml.y);
+#pragma unroll
+            for (int db = 0; db < NDH; ++db)
+#pragma unroll
+              for (int j = 0; j < 4; ++j) A[nb][db][j] = fold_val_tied(f, A[nb][db][j], x[db][j]);
+            M[nb] = f.m_new;
+          }
+        }
+      };
+      fold_chunk(std::integral_constant<int, 0>{});
+      if (two) fold_chunk(std::integral_constant<int, 1>{});
+    };
+    if (wave_on) {
+      if (stream == 0)
+        fold_round(std::integral_constant<int, 0>{});
+      else
+        fold_round(std::integral_constant<int, 1>{});
+    }
+  }
+
+#pragma unroll
+  for (int nb = 0; nb < kNB; ++nb) {
+    const int qp = q0 + kQCols * nb + col;
+    if (wave_on && qp < L) {
+      __bf16* orow = p.out + (static_cast<int64_t>(lo + qp) * p.hq + head) * D + 16 * NDH * stream + 4 * g;
+#pragma unroll
+      for (int db = 0; db < NDH; ++db) {
+        bf16x4 w;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w[j] = finalize_val(A[nb][db][j], Ls[nb]);
+        *reinterpret_cast<bf16x4*>(orow + 16 * db) = w;
+      }
+      if (p.lse != nullptr && g == 0 && stream == 0)
+        p.lse[static_cast<int64_t>(lo + qp) * p.hq + head] = finalize_lse(M[nb], Ls[nb], c);
+    }
+  }
+}
+
 }  // namespace
 
 hipError_t launch_prefill(const PrefillLaunch& a, hipStream_t stream) {
@@ -425,14 +626,34 @@ hipError_t launch_prefill(const PrefillLaunch& a, hipStream_t stream) {
   p.total = a.total_tokens;
   p.c = a.c;
   p.num_seqs = a.num_seqs;
-  const int64_t ntiles = (a.max_seqlen + kWgRows - 1) / kWgRows;
-  const int64_t ngroups = ntiles * a.num_seqs * a.num_kv_heads;
-  const int64_t nblocks = (ngroups + kXcds - 1) / kXcds * kXcds * p.group;
+  // Workgroups with rows in them, at most, for tiles of `rows` rows.
+  const int64_t cus = device_cus();
+  auto tiles = [&](int64_t rows) { return (static_cast<int64_t>(a.max_seqlen) + rows - 1) / rows; };
+  auto busy = [&](int64_t rows) {
+    const int64_t padded = tiles(rows) * a.num_seqs, packed = a.total_tokens / rows + a.num_seqs;
+    return (padded < packed ? padded : packed) * a.num_q_heads;
+  };
+  // The split kernel halves a workgroup's chain of tiles and doubles the
+  // workgroups, each with some 5 us of its own, so it pays while those fit the
+  // CUs at once, or while prefill_kernel's do and the chain is the longer part.
+  // Prefill_kernel against split, us (one sequence, 32/8 heads, d = 128): 128
+  // keys 10.7 / 9.6, 512 22.7 / 15.8, 1000 36.7 / 25.3, 1536 51 / 38, 2048
+  // 66 / 57, 3072 104 / 116; four of 300 keys 17.2 / 20.3; 8192, 8/1 heads
+  // 227 / 171; 32 of 128 keys, which fill half of a 256-row tile, 42.8 / 37.8.
+  const bool split = a.max_seqlen <= kSplitRows || busy(kSplitRows) <= cus ||
+                     (busy(kWgRows) <= cus && a.max_seqlen > 2 * kChunkKeys);
+  const int64_t units = static_cast<int64_t>(a.num_seqs) * a.num_kv_heads;
+  const int64_t ngroups = tiles(split ? kSplitRows : kWgRows) * units;
+  const int64_t nblocks = xcd_grid(ngroups, p.group);
   if (nblocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
   p.ngroups = static_cast<int>(ngroups);
   const dim3 grid(static_cast<unsigned>(nblocks));
   const dim3 block(kWaves * 64);
-  if (a.head_dim == 128)
+  if (split && a.head_dim == 128)
+    hipLaunchKernelGGL(prefill_split_kernel<128>, grid, block, 0, stream, p);
+  else if (split)
+    hipLaunchKernelGGL(prefill_split_kernel<64>, grid, block, 0, stream, p);
+  else if (a.head_dim == 128)
     hipLaunchKernelGGL(prefill_kernel<128>, grid, block, 0, stream, p);
   else
     hipLaunchKernelGGL(prefill_kernel<64>, grid, block, 0, stream, p);

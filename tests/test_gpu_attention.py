@@ -396,3 +396,21 @@ def test_ragged_decode_walk_lists_every_chunk(ua, batch, hkv, group, d, longest)
     none = torch.from_numpy(lens == 0).cuda()
     assert bool((out[none] == 7.0).all()) and bool((lse[none] == 7.0).all())
     assert bool(torch.isfinite(out.float()).all()) and bool(torch.isfinite(lse).all())
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(16, 4, 128), (15, 3, 64), (16, 1, 128)])
+def test_short_calls_give_the_bits_of_large_ones(ua, hq, hkv, d):
+    """A call of few rows walks two chunks at once (128-row tiles): sequences that end at its edges (tiles of 64, rows of
+    128, one to five chunks of 256, so a last round of one chunk and of two) alone equal themselves in a pack that takes
+    the other kernel."""
+    import torch
+    lens = [1, 63, 65, 127, 128, 129, 255, 256, 257, 300, 511, 513, 640, 769, 1024, 1025, 1200]
+    cu = inputs.cu_seqlens(lens)
+    T = int(cu[-1])
+    q, k, v = (gu.dev(inputs.normal_bf16((T, h, d), 1.0, 77, hq, d, i)) for i, h in enumerate((hq, hkv, hkv)))
+    full, full_lse = ua.prefill(q, k, v, gu.dev_i32(cu), max(lens), return_lse=True)
+    for lo, n in zip(cu[:-1], lens):
+        rows = slice(int(lo), int(lo) + n)
+        out, lse = ua.prefill(q[rows], k[rows], v[rows], gu.dev_i32([0, n]), n, return_lse=True)
+        assert torch.equal(out.view(torch.int16), full[rows].view(torch.int16)), n
+        assert torch.equal(lse.view(torch.int32), full_lse[rows].view(torch.int32)), n
