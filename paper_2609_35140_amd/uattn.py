@@ -94,15 +94,23 @@ def _check(code: int):
         raise UattnError(status_string(code))
 
 
+# What a small call costs here is Python: of 12 us for a decode-sized kv_write,
+# 4 were the C call with its launch, 3 the Stream object that
+# torch.cuda.current_stream() builds, the rest checks whose messages were
+# formatted whether or not they failed.  So the current stream's handle is asked
+# for itself, and a message is formed only by the check that fails.
 def _stream(stream) -> int:
-    import torch
     if stream is None:
+        import torch
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None:
+            return raw(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
     return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _ptr(t) -> Optional[int]:
-    return None if t is None else int(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _need(cond: bool, msg: str):
@@ -112,9 +120,23 @@ def _need(cond: bool, msg: str):
 
 def _bf16_cuda(t, name):
     import torch
+    if t.is_cuda and t.dtype == torch.bfloat16 and t.is_contiguous():
+        return
     _need(t.is_cuda, f"{name} must be a GPU tensor")
     _need(t.dtype == torch.bfloat16, f"{name} must be bfloat16")
-    _need(t.is_contiguous(), f"{name} must be contiguous")
+    _need(False, f"{name} must be contiguous")
+
+
+def _i32_cuda(t, name, msg="must be contiguous int32 on the GPU"):
+    import torch
+    if not (t.dtype == torch.int32 and t.is_cuda and t.is_contiguous()):
+        raise ValueError(f"{name} {msg}")
+
+
+def _bf16_rows(t, name):
+    import torch
+    if not (t.is_cuda and t.dtype == torch.bfloat16 and t.dim() == 2 and t.stride(1) == 1):
+        raise ValueError(f"{name} must be a 2-D bfloat16 GPU tensor with contiguous rows")
 
 
 def default_scale(head_dim: int) -> float:
@@ -129,8 +151,9 @@ def prefill(q, k, v, cu_seqlens, max_seqlen: int, softmax_scale: Optional[float]
     Returns out [T,Hq,d] (and lse [T,Hq] fp32 if requested).
     """
     import torch
-    for name, t in (("q", q), ("k", k), ("v", v)):
-        _bf16_cuda(t, name)
+    _bf16_cuda(q, "q")
+    _bf16_cuda(k, "k")
+    _bf16_cuda(v, "v")
     _need(q.dim() == 3 and k.dim() == 3 and v.dim() == 3, "q/k/v must be [T, H, d]")
     T, hq, d = q.shape
     _need(k.shape == v.shape and k.shape[0] == T and k.shape[2] == d, "k/v shape mismatch")
@@ -261,14 +284,15 @@ def decode(q, k_pages, v_pages, block_table, seqlens, max_seqlen: int, softmax_s
     fresh one is allocated when not given.
     """
     import torch
-    for name, t in (("q", q), ("k_pages", k_pages), ("v_pages", v_pages)):
-        _bf16_cuda(t, name)
+    _bf16_cuda(q, "q")
+    _bf16_cuda(k_pages, "k_pages")
+    _bf16_cuda(v_pages, "v_pages")
     _need(q.dim() == 3 and k_pages.dim() == 4 and v_pages.shape == k_pages.shape, "shapes: q [B,Hq,d], pages [P,Hkv,page,d]")
     B, hq, d = q.shape
     _, hkv, page, d2 = k_pages.shape
     _need(d2 == d, "head_dim mismatch")
-    for name, t in (("block_table", block_table), ("seqlens", seqlens)):
-        _need(t.dtype == torch.int32 and t.is_cuda and t.is_contiguous(), f"{name} must be contiguous int32 on the GPU")
+    _i32_cuda(block_table, "block_table")
+    _i32_cuda(seqlens, "seqlens")
     _need(block_table.dim() == 2 and block_table.shape[0] == B and seqlens.shape == (B,), "block_table/seqlens shape")
     if softmax_scale is None:
         softmax_scale = default_scale(d)
@@ -304,14 +328,15 @@ def decode_noalloc(q, k_pages, v_pages, block_table, seqlens, max_seqlen: int, s
     ``out``/``lse`` to keep this binding from allocating them).  Arguments and
     results as for :func:`decode`."""
     import torch
-    for name, t in (("q", q), ("k_pages", k_pages), ("v_pages", v_pages)):
-        _bf16_cuda(t, name)
+    _bf16_cuda(q, "q")
+    _bf16_cuda(k_pages, "k_pages")
+    _bf16_cuda(v_pages, "v_pages")
     _need(q.dim() == 3 and k_pages.dim() == 4 and v_pages.shape == k_pages.shape, "shapes: q [B,Hq,d], pages [P,Hkv,page,d]")
     B, hq, d = q.shape
     _, hkv, page, d2 = k_pages.shape
     _need(d2 == d, "head_dim mismatch")
-    for name, t in (("block_table", block_table), ("seqlens", seqlens)):
-        _need(t.dtype == torch.int32 and t.is_cuda and t.is_contiguous(), f"{name} must be contiguous int32 on the GPU")
+    _i32_cuda(block_table, "block_table")
+    _i32_cuda(seqlens, "seqlens")
     _need(block_table.dim() == 2 and block_table.shape[0] == B and seqlens.shape == (B,), "block_table/seqlens shape")
     if softmax_scale is None:
         softmax_scale = default_scale(d)
@@ -353,19 +378,19 @@ def kv_write(k_new, v_new, block_table, seq_idx, positions, k_pages, v_pages, st
       k_pages, v_pages  [P, Hkv, page, d] bf16, updated in place
     """
     import torch
-    for name, t in (("k_pages", k_pages), ("v_pages", v_pages)):
-        _bf16_cuda(t, name)
-    for name, t in (("k_new", k_new), ("v_new", v_new)):
-        _need(t.is_cuda and t.dtype == torch.bfloat16, f"{name} must be a bfloat16 GPU tensor")
+    _bf16_cuda(k_pages, "k_pages")
+    _bf16_cuda(v_pages, "v_pages")
+    _need(k_new.is_cuda and k_new.dtype == torch.bfloat16, "k_new must be a bfloat16 GPU tensor")
+    _need(v_new.is_cuda and v_new.dtype == torch.bfloat16, "v_new must be a bfloat16 GPU tensor")
     _need(k_new.dim() == 3 and v_new.shape == k_new.shape, "k_new/v_new must be [N,Hkv,d]")
     N, hkv, d = k_new.shape
     _need(k_new.stride(2) == 1 and k_new.stride(1) == d and v_new.stride() == k_new.stride(),
           "k_new/v_new: heads and d must be contiguous, both with the same token stride")
     P, hkv2, page, d2 = k_pages.shape
-    _need(hkv2 == hkv and d2 == d and v_pages.shape == k_pages.shape and k_pages.is_contiguous()
-          and v_pages.is_contiguous(), "page shapes")
-    for name, t in (("block_table", block_table), ("seq_idx", seq_idx), ("positions", positions)):
-        _need(t.dtype == torch.int32 and t.is_cuda and t.is_contiguous(), f"{name} must be int32 on the GPU")
+    _need(hkv2 == hkv and d2 == d and v_pages.shape == k_pages.shape, "page shapes")
+    _i32_cuda(block_table, "block_table", "must be int32 on the GPU")
+    _i32_cuda(seq_idx, "seq_idx", "must be int32 on the GPU")
+    _i32_cuda(positions, "positions", "must be int32 on the GPU")
     _need(block_table.dim() == 2 and seq_idx.shape == (N,) and positions.shape == (N,), "index shapes")
     B, maxp = block_table.shape
     _check(_load().uattn_kv_write(_ptr(k_new), _ptr(v_new), k_new.stride(0), _ptr(block_table), _ptr(seq_idx),
@@ -393,8 +418,10 @@ def qk_norm_rope(q, k, positions, q_weight, k_weight, cos_sin, eps: float = 1e-6
       cos_sin [max_position, d/2, 2] fp32.  Outputs may be q and k themselves (in place).
     """
     import torch
-    for name, t in (("q", q), ("k", k), ("q_weight", q_weight), ("k_weight", k_weight)):
-        _bf16_cuda(t, name)
+    _bf16_cuda(q, "q")
+    _bf16_cuda(k, "k")
+    _bf16_cuda(q_weight, "q_weight")
+    _bf16_cuda(k_weight, "k_weight")
     _need(q.dim() == 3 and k.dim() == 3 and q.shape[0] == k.shape[0] and q.shape[2] == k.shape[2], "q/k shapes")
     T, hq, d = q.shape
     hkv = k.shape[1]
@@ -420,9 +447,8 @@ def lm_head(hidden, weight, out=None, stream=None):
       hidden [T, H] bf16, weight [V, H] bf16 (rows may be strided); out [T, V] bf16 (row stride a multiple of 8).
     """
     import torch
-    for name, t in (("hidden", hidden), ("weight", weight)):
-        _need(t.is_cuda and t.dtype == torch.bfloat16 and t.dim() == 2 and t.stride(1) == 1,
-              f"{name} must be a 2-D bfloat16 GPU tensor with contiguous rows")
+    _bf16_rows(hidden, "hidden")
+    _bf16_rows(weight, "weight")
     T, H = hidden.shape
     V, H2 = weight.shape
     _need(H2 == H, "hidden and weight widths differ")
@@ -448,9 +474,8 @@ def lm_head_logprob(hidden, weight, targets, inv_temperature: float = 1.0, out=N
       of 8), when given, also receives the logits.
     """
     import torch
-    for name, t in (("hidden", hidden), ("weight", weight)):
-        _need(t.is_cuda and t.dtype == torch.bfloat16 and t.dim() == 2 and t.stride(1) == 1,
-              f"{name} must be a 2-D bfloat16 GPU tensor with contiguous rows")
+    _bf16_rows(hidden, "hidden")
+    _bf16_rows(weight, "weight")
     T, H = hidden.shape
     V, H2 = weight.shape
     _need(H2 == H, "hidden and weight widths differ")
