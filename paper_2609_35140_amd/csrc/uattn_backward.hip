@@ -146,7 +146,8 @@ struct BwdParams {
   __bf16* dk;
   __bf16* dv;
   int hq, hkv, group, total, num_seqs;
-  int kv_units, dq_units;  // work units of the two kernels (see xcd_unit)
+  // work units of the two kernels (see xcd_unit), and the key or query tiles to one
+  int kv_units, dq_units, kt_group, qt_group;
   float c, scale;
 };
 
@@ -327,9 +328,9 @@ __global__ __launch_bounds__(kKvWaves * 64, 1) void bwd_dkdv_kernel(BwdParams p)
   __shared__ __attribute__((aligned(1024))) __bf16 lds[kStages * kStageElems];
   __shared__ __attribute__((aligned(1024))) f32x4 pbuf[kKvPairs][8][64];  // P(t), in each lane's score layout
 
-  const XcdUnit w = xcd_unit(blockIdx.x, kKeyTileGroup);
+  const XcdUnit w = xcd_unit(blockIdx.x, p.kt_group);
   if (w.unit >= p.kv_units) return;
-  const int kt = w.unit / (p.num_seqs * p.hkv) * kKeyTileGroup + w.member;
+  const int kt = w.unit / (p.num_seqs * p.hkv) * p.kt_group + w.member;
   const int seq = (w.unit / p.hkv) % p.num_seqs;
   const int kvh = w.unit % p.hkv;
   int lo, L;
@@ -529,10 +530,10 @@ __global__ __launch_bounds__(kDqWaves * 64, 1) void bwd_dq_kernel(BwdParams p) {
   constexpr int kStageElems = 2 * BT::kElems;  // K tile, V tile
   __shared__ __attribute__((aligned(1024))) __bf16 lds[2 * kStageElems];
 
-  const XcdUnit w = xcd_unit(blockIdx.x, kDqTileGroup * p.group);
+  const XcdUnit w = xcd_unit(blockIdx.x, p.qt_group * p.group);
   if (w.unit >= p.dq_units) return;
   // query tiles counted from the end: longest work first
-  const int zrev = w.unit / (p.num_seqs * p.hkv) * kDqTileGroup + w.member / p.group;
+  const int zrev = w.unit / (p.num_seqs * p.hkv) * p.qt_group + w.member / p.group;
   const int seq = (w.unit / p.hkv) % p.num_seqs;
   const int kvh = w.unit % p.hkv;
   const int head = kvh * p.group + w.member % p.group;
@@ -683,11 +684,14 @@ hipError_t launch_backward_d(const BwdParams& p0, int max_seqlen, hipStream_t st
   const int64_t nprep = (rows + kPrepRows - 1) / kPrepRows;
   BwdParams p = p0;
   const int64_t ktiles = (static_cast<int64_t>(max_seqlen) + kKeyTile - 1) / kKeyTile;
-  const int64_t kv_units = (ktiles + kKeyTileGroup - 1) / kKeyTileGroup * p.num_seqs * p.hkv;
-  const int64_t nkv = xcd_grid(kv_units, kKeyTileGroup);
+  const int64_t streams = static_cast<int64_t>(p.num_seqs) * p.hkv;
+  p.kt_group = unit_tiles(streams, kKeyTileGroup);
+  p.qt_group = unit_tiles(streams, kDqTileGroup);
+  const int64_t kv_units = (ktiles + p.kt_group - 1) / p.kt_group * streams;
+  const int64_t nkv = xcd_grid(kv_units, p.kt_group);
   const int64_t qtiles = (static_cast<int64_t>(max_seqlen) + kDqRows - 1) / kDqRows;
-  const int64_t dq_units = (qtiles + kDqTileGroup - 1) / kDqTileGroup * p.num_seqs * p.hkv;
-  const int64_t ndq = xcd_grid(dq_units, kDqTileGroup * p.group);
+  const int64_t dq_units = (qtiles + p.qt_group - 1) / p.qt_group * streams;
+  const int64_t ndq = xcd_grid(dq_units, p.qt_group * p.group);
   if (nprep > 0x7FFFFFFF || nkv > 0x7FFFFFFF || ndq > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
   p.kv_units = static_cast<int>(kv_units);
   p.dq_units = static_cast<int>(dq_units);

@@ -34,6 +34,10 @@ __device__ __forceinline__ XcdUnit xcd_unit(int pid, int members) {
   const int j = pid / kXcds;
   return {j / members * kXcds + pid % kXcds, j % members};
 }
+// Tiles of a stream (a sequence's kv head) to a unit: `most`, or 1 where a
+// launch has fewer streams than XCDs, whose longest tiles would otherwise
+// all land on the first ones.
+inline int unit_tiles(int64_t streams, int most) { return streams >= kXcds ? most : 1; }
 // Workgroups of a launch over `units` units (ids past the last unit do nothing).
 inline int64_t xcd_grid(int64_t units, int64_t members) { return (units + kXcds - 1) / kXcds * kXcds * members; }
 
