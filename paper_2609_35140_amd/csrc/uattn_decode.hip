@@ -331,7 +331,9 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(DecodeParams p) {
 
 constexpr int64_t kLdsBytesPerCu = 160 * 1024;
 constexpr int kLenScanMax = 4096;  // batches up to this size skip chunks past their longest entry
-constexpr int kListMax = 1024;     // and up to this size every empty chunk
+constexpr int kListMax = 1024;     // and up to this size, and this many
+constexpr int kListRuns = 1024;    // chunks, every empty chunk
+static_assert(kListRuns >= kListMax, "a run is a chunk's pairs or an entry's");
 
 // Buffered variant, for long walks: finished partials wait in LDS and go to
 // the workspace in one burst per drain, instead of a few stores per item mixed
@@ -340,7 +342,7 @@ constexpr int kListMax = 1024;     // and up to this size every empty chunk
 // the walk.  Room for 16 items of 8 q heads x 128 d.
 constexpr int kBufFloats = 17152;
 
-template <int D, int NB, bool kBuf>
+template <int D, int NB, bool kBuf, bool kList>
 struct DecodeSmem {
   using TL = TileLayout<D>;
   static constexpr int kMaxPend = 32;          // finished partials awaiting their arrival count
@@ -349,13 +351,26 @@ struct DecodeSmem {
   float tmax[kTilesPerChunk][NB][kQCols];      // column maxima of tile t's scores
   int32_t pend[kMaxPend][3];                   // (b * Hkv + kv head, chunk count, chunk)
   int32_t flag[kMaxPend];
-  int32_t lenmax[4];                           // per wave: the longest entry it read, or its entries' chunks
-  int32_t first[kListMax + 1];                 // chunks of the entries before each entry
+  int32_t lenmax[4];                           // per wave: the longest entry it read
+  // kList: entries' chunk counts; pairs up to the end of each run
+  alignas(16) uint16_t nch[kList ? kListMax : 8];
+  int32_t upto[kList ? kListRuns : 1];
   // kBuf: per pending item, G rows of D + 4 floats (acc; the padding spreads
   // the 16 heads of a store over the banks), then G (m, l) pairs
   alignas(16) float pbuf[kBuf ? kBufFloats : 4];
 };
 
+
+// Sum over lanes 0 .. lane, every lane active.
+__device__ __forceinline__ int wave_inclusive_sum(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111 /* row_shr:1 */, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142 /* row_bcast:15 */, 0xA, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143 /* row_bcast:31 */, 0xC, 0xF, false);
+  return x;
+}
 
 // One item as a wave sees it (all fields wave-uniform).
 struct Item {
@@ -365,11 +380,11 @@ struct Item {
   int ntiles;  // tiles of this chunk that hold keys (0: nothing to do)
 };
 
-template <int D, int NB, bool kBuf>
+template <int D, int NB, bool kBuf, bool kList>
 __global__ __launch_bounds__(256, kBuf ? 1 : 2) void decode_kernel(DecodeParams p, const int32_t* __restrict__ seqlens,
                                                                    const int32_t* __restrict__ block_table) {
   using TL = TileLayout<D>;
-  using SM = DecodeSmem<D, NB, kBuf>;
+  using SM = DecodeSmem<D, NB, kBuf, kList>;
   constexpr int KS = D / 32;                   // K steps of the score product
   constexpr int NDBW = D / 16 / 4;             // 16-wide d blocks of the output per wave
   constexpr int kVInstr = TL::kPieces;         // 1 KB direct-to-LDS instructions per V tile
@@ -387,76 +402,100 @@ __global__ __launch_bounds__(256, kBuf ? 1 : 2) void decode_kernel(DecodeParams 
   const __bf16* zero = reinterpret_cast<const __bf16*>(g_zero_rows);
 
   // Which item is which.  A short walk takes the items chunk-major over the
-  // full grid of max_seqlen's chunks, the empty ones among them.  When this
-  // workgroup's walk is longer than two items, it reads the batch's lengths
-  // first and walks only chunks that hold keys, entry by entry: an empty item
-  // costs most of a round trip, and in a ragged batch about half are empty
-  // (64 entries of 1280-16384 keys, 32/8 heads, the whole layer's step: 597 us
-  // with them in the walk, 426 without).
-  // kListMax bounds the LDS for the entries' first chunks; larger batches only
-  // drop the chunks past the longest entry.
+  // full grid of max_seqlen's chunks, the empty ones among them.  A longer one
+  // (kList, see launch_decode) reads the batch's lengths first and walks only
+  // the (entry, chunk) pairs that hold keys: an empty item costs most of a
+  // round trip, and in a ragged batch about half are empty (64 entries of
+  // 1280-16384 keys, 32/8 heads, the whole layer's step: 609 us with them in
+  // the walk, 437 without).  The pairs are listed in runs, those of a chunk:
+  // entry by entry, an entry's merge falls into the walk of the workgroup that
+  // arrives last (8 steps of 8 x 8000 keys 461 us against 372).  Buffered walks,
+  // which merge in a kernel of their own, list the pairs of an entry, whose
+  // place takes fewer steps to find (4 steps of 8 x 32K keys, 64/8 heads: 844 us
+  // chunk by chunk, 834 so).
+  // Batches past kListMax only drop the chunks past the longest entry.
   int ncand = ncand_all;
-  bool listed = false;
-  int lane_end = 0;   // listed: chunks of the entries before (lane + 1) * span
-  int span = 1;       // entries to a lane
-  if (p.nchunk_max > 1 && p.batch <= kLenScanMax && ncand_all > 2 * stride) {
-    listed = p.batch <= kListMax;
-    int mine = 0, lmax = 0;
-    constexpr int kPer = kListMax / 256;
-    if (listed) {
-      int part[kPer];
-#pragma unroll
-      for (int i = 0; i < kPer; ++i) {
-        const int e = kPer * tid + i;
-        const int n = e < p.batch ? min(p.seqlens[e], p.max_seqlen) : 0;
-        part[i] = mine;
-        mine += n > 0 ? (n + kChunkKeys - 1) / kChunkKeys : 0;
-      }
-      int incl = mine;
-#pragma unroll
-      for (int sh = 1; sh < 64; sh <<= 1) {
-        const int o = __shfl_up(incl, sh, 64);
-        if (lane >= sh) incl += o;
-      }
-      if (lane == 63) sm.lenmax[wave] = incl;
-      __syncthreads();
-      int before = incl - mine;
-#pragma unroll
-      for (int w = 0; w < 4; ++w)
-        if (w < wave) before += sm.lenmax[w];
-#pragma unroll
-      for (int i = 0; i < kPer; ++i) sm.first[kPer * tid + i] = before + part[i];
-      if (tid == 255) sm.first[kListMax] = before + mine;
-      __syncthreads();
-      span = (p.batch + 63) / 64;
-      lane_end = sm.first[min((lane + 1) * span, kListMax)];
-      ncand = __builtin_amdgcn_readfirstlane(sm.first[kListMax]) * p.hkv;
-    } else {
-      for (int i = tid; i < p.batch; i += 256) lmax = max(lmax, p.seqlens[i]);
-#pragma unroll
-      for (int m = 32; m >= 1; m >>= 1) lmax = max(lmax, __shfl_xor(lmax, m));
-      if (lane == 0) sm.lenmax[wave] = lmax;
-      __syncthreads();
-      lmax = max(max(sm.lenmax[0], sm.lenmax[1]), max(sm.lenmax[2], sm.lenmax[3]));
-      const int nch = min(max((min(lmax, p.max_seqlen) + kChunkKeys - 1) / kChunkKeys, 1), p.nchunk_max);
-      ncand = __builtin_amdgcn_readfirstlane(per_chunk * nch);
+  const int nruns = kBuf ? p.batch : p.nchunk_max;
+  int lane_end = 0;  // kList: upto[] of the last of this lane's `span` runs
+  int span = 1;      // runs to a lane
+  int nch_lane = 0;  // kList: chunk count of entry `lane`
+  if constexpr (kList) {
+    for (int e = tid; e < (p.batch + 63) / 64 * 64; e += 256) {
+      const int n = e < p.batch ? min(p.seqlens[e], p.max_seqlen) : 0;
+      sm.nch[e] = static_cast<uint16_t>(n > 0 ? (n + kChunkKeys - 1) / kChunkKeys : 0);
     }
+    __syncthreads();
+    nch_lane = sm.nch[lane];
+    // every wave computes the same prefix for itself (64 runs at a time)
+    // and writes the same words, so no barrier is needed before it reads them
+    int total = 0;
+#pragma unroll 1
+    for (int r0 = 0; r0 < nruns; r0 += 64) {
+      const uint32_t run = r0 + lane;
+      int mine = 0;  // the run's pairs
+      if constexpr (kBuf) {
+        mine = sm.nch[run];
+      } else {
+        for (int e = 0; e < p.batch; e += 8) {
+          const u32x4 v = *reinterpret_cast<const u32x4*>(&sm.nch[e]);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) mine += ((v[i] & 0xFFFFu) > run ? 1 : 0) + ((v[i] >> 16) > run ? 1 : 0);
+        }
+      }
+      lane_end = total + wave_inclusive_sum(mine);
+      if (run < static_cast<uint32_t>(nruns)) sm.upto[run] = lane_end;
+      total = __builtin_amdgcn_readlane(lane_end, 63);
+    }
+    span = (nruns + 63) / 64;
+    if (span > 1) lane_end = sm.upto[min((lane + 1) * span, nruns) - 1];
+    ncand = total * p.hkv;
+  } else if (p.nchunk_max > 1 && p.batch <= kLenScanMax && ncand_all > 2 * stride) {
+    int lmax = 0;
+    for (int i = tid; i < p.batch; i += 256) lmax = max(lmax, p.seqlens[i]);
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) lmax = max(lmax, __shfl_xor(lmax, m));
+    if (lane == 0) sm.lenmax[wave] = lmax;
+    __syncthreads();
+    lmax = max(max(sm.lenmax[0], sm.lenmax[1]), max(sm.lenmax[2], sm.lenmax[3]));
+    const int nch = min(max((min(lmax, p.max_seqlen) + kChunkKeys - 1) / kChunkKeys, 1), p.nchunk_max);
+    ncand = __builtin_amdgcn_readfirstlane(per_chunk * nch);
   }
-  // (chunk, entry, kv head) of item `it`, wave-uniform
+  // (chunk, entry, kv head) of item `it` of the list, wave-uniform
   struct Where {
     int chunk, b, kvh;
   };
   auto locate = [&](int it) -> Where {
-    if (!listed) return {it / per_chunk, (it % per_chunk) / p.hkv, it % p.hkv};
-    const int u = it / p.hkv;  // position in the list of chunks
-    // the entry is the last whose first chunk is not after u: the lane whose
-    // entries contain it, then the entry among the lane's
-    int b = min(__builtin_popcountll(__builtin_amdgcn_ballot_w64(lane_end <= u)) * span, p.batch - 1);
+    const int u = it / p.hkv;
+    // the run is the last whose first pair is not after u: the lane whose runs
+    // contain it, then the run among the lane's; `before`: the pairs of the
+    // runs before it
+    const int l = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane_end <= u));
+    int c = min(l * span, nruns - 1);
+    int before = l == 0 ? 0 : __builtin_amdgcn_readlane(lane_end, l - 1);
     if (span > 1) {
-      const int end = sm.first[min(b + lane + 1, kListMax)];
-      b = min(b + __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < span && end <= u)), p.batch - 1);
+      const int end = sm.upto[min(c + lane, nruns - 1)];
+      const int j = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < span && end <= u));
+      if (j > 0) before = __builtin_amdgcn_readlane(end, j - 1);
+      c = min(c + j, nruns - 1);
     }
-    return {u - __builtin_amdgcn_readfirstlane(sm.first[b]), b, it % p.hkv};
+    if constexpr (kBuf) return {u - before, c, it % p.hkv};
+    // the entry is the k-th that has this chunk
+    int k = u - before;
+    int b0 = 0;
+    bool has = nch_lane > c;
+    for (;;) {
+      const uint64_t mask = __builtin_amdgcn_ballot_w64(has);
+      const int n = __builtin_popcountll(mask);
+      if (k < n || b0 + 64 >= p.batch) {
+        const int below = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
+                                                    __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0));
+        const uint64_t at = __builtin_amdgcn_ballot_w64(has && below == k);
+        return {c, min(b0 + max(__builtin_ffsll(static_cast<long long>(at)) - 1, 0), p.batch - 1), it % p.hkv};
+      }
+      k -= n;
+      b0 += 64;
+      has = sm.nch[b0 + lane] > c;
+    }
   };
 
   // An item's descriptor, for this wave: the entry length and the page of
@@ -469,23 +508,38 @@ __global__ __launch_bounds__(256, kBuf ? 1 : 2) void decode_kernel(DecodeParams 
     int len;
     int page[kKeyBlocks];
   };
+  auto in_grid = [&](int it) { return kList ? it : min(it, ncand_all - 1); };
   auto load_desc = [&](int it) -> Desc {
     Desc d;
-    d.at = locate(min(it, max(ncand, 1) - 1));
-    const int32_t* row = block_table + static_cast<int64_t>(d.at.b) * p.maxp;
-    d.len = it < ncand ? seqlens[d.at.b] : 0;
+    int chunk, b;
+    if constexpr (kList) {
+      d.at = locate(min(it, max(ncand, 1) - 1));
+      chunk = d.at.chunk;
+      b = d.at.b;
+    } else {
+      chunk = it / per_chunk;
+      b = (it % per_chunk) / p.hkv;
+    }
+    const int32_t* row = block_table + static_cast<int64_t>(b) * p.maxp;
+    d.len = seqlens[b];
 #pragma unroll
     for (int kb = 0; kb < kKeyBlocks; ++kb) {
-      const int pos = (d.at.chunk * kTilesPerChunk + wave) * kTileKeys + 16 * kb;
+      const int pos = (chunk * kTilesPerChunk + wave) * kTileKeys + 16 * kb;
       d.page[kb] = row[min(pos >> p.page_shift, p.maxp - 1)];
     }
     return d;
   };
   auto make_item = [&](int it, const Desc& desc) -> Item {
     Item r;
-    r.chunk = desc.at.chunk;
-    r.b = desc.at.b;
-    r.kvh = desc.at.kvh;
+    if constexpr (kList) {
+      r.chunk = desc.at.chunk;
+      r.b = desc.at.b;
+      r.kvh = desc.at.kvh;
+    } else {
+      r.chunk = it / per_chunk;
+      r.b = (it % per_chunk) / p.hkv;
+      r.kvh = it % p.hkv;
+    }
     r.n = it < ncand ? min(desc.len, p.max_seqlen) : 0;
     r.nch = (r.n + kChunkKeys - 1) / kChunkKeys;
     r.ntiles = (r.n >= 1 && r.chunk < r.nch) ? min(kTilesPerChunk, (r.n - 1) / kTileKeys - r.chunk * kTilesPerChunk + 1) : 0;
@@ -607,13 +661,13 @@ __global__ __launch_bounds__(256, kBuf ? 1 : 2) void decode_kernel(DecodeParams 
   // and PV phases.
   Desc desc = load_desc(blockIdx.x);
   Item cur = make_item(blockIdx.x, desc);
-  Desc desc_next = load_desc(blockIdx.x + stride);
+  Desc desc_next = load_desc(in_grid(blockIdx.x + stride));
   Operands op;
   issue_ops(cur, desc, op);
 #pragma unroll 1
   for (int item = blockIdx.x; item < ncand; item += stride) {
     const Item next = make_item(item + stride, desc_next);   // empty past the walk
-    const Desc desc_after = load_desc(item + 2 * stride);
+    const Desc desc_after = load_desc(in_grid(item + 2 * stride));
     const int tile = cur.chunk * kTilesPerChunk + wave;  // this wave's tile (sequence-relative)
     const bool tile_on = wave < cur.ntiles;
 
@@ -829,36 +883,50 @@ hipError_t launch_decode(const DecodeLaunch& a, hipStream_t stream) {
   // long walks (at least 16 items per CU): the buffered variant, one
   // workgroup per CU
   const bool buffered = a.nchunk_max > 1 && ncand >= 16 * static_cast<int64_t>(a.num_cus);
-  auto launch = [&](auto kernel, size_t smem_bytes) {
-    // persistent grid: as many workgroups as the CUs hold at once (LDS-bound)
-    const int64_t per_cu = 2 * smem_bytes + 1024 <= kLdsBytesPerCu ? 2 : 1;
-    const int64_t slots = per_cu * a.num_cus;
-    const dim3 grid(static_cast<unsigned>(ncand < slots ? ncand : slots));
-    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, p, p.seqlens, p.bt);
-  };
-  auto pick = [&](auto d_const, auto nb_const) {
+  auto pick = [&](auto d_const, auto nb_const, auto buf_const) {
     constexpr int kD = decltype(d_const)::value, kNB = decltype(nb_const)::value;
-    if (buffered) {
-      launch(decode_kernel<kD, kNB, true>, sizeof(DecodeSmem<kD, kNB, true>));
+    constexpr bool kBuf = decltype(buf_const)::value;
+    // persistent grid: as many workgroups as the CUs hold at once (LDS-bound)
+    auto grid_of = [&](size_t smem_bytes) {
+      const int64_t slots = (2 * smem_bytes + 1024 <= kLdsBytesPerCu ? 2 : 1) * static_cast<int64_t>(a.num_cus);
+      return ncand < slots ? ncand : slots;
+    };
+    // The list of pairs with keys pays where a workgroup takes more than two
+    // items of the grid: 16 entries of 400-3000 keys, 32/8 heads, 8 steps 220 us
+    // without it, 210 with; with all 16 at 3000 it costs 1% (283, 285.5).
+    // A shorter walk has too few items to earn the scan: 16 steps of 6 x 1824
+    // keys, 64/8 heads, 239.4 us, 243.9 with the list's code in that kernel.
+    const int64_t grid_list = grid_of(sizeof(DecodeSmem<kD, kNB, kBuf, true>));
+    if (a.nchunk_max > 1 && a.nchunk_max <= kListRuns && a.batch <= kListMax && ncand > 2 * grid_list)
+      hipLaunchKernelGGL((decode_kernel<kD, kNB, kBuf, true>), dim3(static_cast<unsigned>(grid_list)), dim3(256), 0, stream,
+                         p, p.seqlens, p.bt);
+    else
+      hipLaunchKernelGGL((decode_kernel<kD, kNB, kBuf, false>),
+                         dim3(static_cast<unsigned>(grid_of(sizeof(DecodeSmem<kD, kNB, kBuf, false>)))), dim3(256), 0,
+                         stream, p, p.seqlens, p.bt);
+    if constexpr (kBuf) {
       constexpr int kRows = 256 / kD;
       const int64_t rows = static_cast<int64_t>(a.batch) * a.num_q_heads;
       hipLaunchKernelGGL(decode_merge_kernel<kD>, dim3(static_cast<unsigned>((rows + kRows - 1) / kRows)), dim3(256), 0,
                          stream, p);
-    } else {
-      launch(decode_kernel<kD, kNB, false>, sizeof(DecodeSmem<kD, kNB, false>));
     }
   };
-  if (a.head_dim == 128) {
+  auto pick_d = [&](auto d_const) {
+    auto pick_nb = [&](auto nb_const) {
+      if (buffered)
+        pick(d_const, nb_const, std::true_type{});
+      else
+        pick(d_const, nb_const, std::false_type{});
+    };
     if (two)
-      pick(std::integral_constant<int, 128>{}, std::integral_constant<int, 2>{});
+      pick_nb(std::integral_constant<int, 2>{});
     else
-      pick(std::integral_constant<int, 128>{}, std::integral_constant<int, 1>{});
-  } else {
-    if (two)
-      pick(std::integral_constant<int, 64>{}, std::integral_constant<int, 2>{});
-    else
-      pick(std::integral_constant<int, 64>{}, std::integral_constant<int, 1>{});
-  }
+      pick_nb(std::integral_constant<int, 1>{});
+  };
+  if (a.head_dim == 128)
+    pick_d(std::integral_constant<int, 128>{});
+  else
+    pick_d(std::integral_constant<int, 64>{});
   return hipGetLastError();
 }
 

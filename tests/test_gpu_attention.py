@@ -398,6 +398,27 @@ def test_ragged_decode_walk_lists_every_chunk(ua, batch, hkv, group, d, longest)
     assert bool(torch.isfinite(out.float()).all()) and bool(torch.isfinite(lse).all())
 
 
+@pytest.mark.parametrize("batch,hkv,group,d,longest", [(5, 8, 4, 128, 20000), (12, 8, 8, 128, 17000), (70, 8, 2, 64, 16640)])
+def test_listed_walk_over_many_chunks(ua, batch, hkv, group, d, longest):
+    """More than 64 chunks, so several to a lane of the list, with one and with several blocks of 64 entries: every entry
+    equals itself alone, in a call short enough to take the plain grid."""
+    import torch
+    page = 64
+    hq = hkv * group
+    lens = inputs.rng(78, batch).integers(0, longest, size=batch, endpoint=True)
+    lens[1], lens[-1] = 0, longest
+    table = gu.dev_i32(inputs.rng(79, batch).integers(0, 97, size=(batch, (longest + page - 1) // page)))
+    q = inputs.normal_bf16_device((batch, hq, d), 1.0, 80, batch)
+    kp, vp = (inputs.normal_bf16_device((97, hkv, page, d), 1.0, 81 + i, batch) for i in range(2))
+    out, lse = torch.full_like(q, 7.0), torch.full((batch, hq), 7.0, dtype=torch.float32, device="cuda")
+    ua.decode(q, kp, vp, table, gu.dev_i32(lens), longest, out=out, lse=lse)
+    for i in range(batch):
+        o, e = torch.full_like(q[i:i + 1], 7.0), torch.full_like(lse[i:i + 1], 7.0)
+        ua.decode(q[i:i + 1], kp, vp, table[i:i + 1], gu.dev_i32(lens[i:i + 1]), max(int(lens[i]), 1), out=o, lse=e)
+        assert torch.equal(o.view(torch.int16), out[i:i + 1].view(torch.int16)), i
+        assert torch.equal(e.view(torch.int32), lse[i:i + 1].view(torch.int32)), i
+
+
 @pytest.mark.parametrize("hq,hkv,d", [(16, 4, 128), (15, 3, 64), (16, 1, 128)])
 def test_short_calls_give_the_bits_of_large_ones(ua, hq, hkv, d):
     """A call of few rows walks two chunks at once (128-row tiles): sequences that end at its edges (tiles of 64, rows of
