@@ -68,6 +68,24 @@ def test_matches_oracle(ua, T, hq, hkv, d, sigma, eps):
     torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("T,hq,hkv,d", [(160, 1, 1, 64), (160, 7, 3, 128), (160, 9, 1, 64), (96, 50, 5, 128), (160, 97, 1, 64)])
+def test_head_counts_match_oracle(ua, T, hq, hkv, d):
+    """Items of 4 (d 128) or 8 (d 64) head rows that the heads do not fill, waves without an item, and more than one and
+    two rounds of three items to a wave.  A normalized value one bf16 unit apart (at most 2^-7 of it) moves the rotated
+    pair by at most that part of its length, which the rotation keeps, and rounding the result adds half as much."""
+    x = {n: inputs.normal_bf16((T, h, d), 1.0, 74, T, n) for n, h in enumerate((hq, hkv))}
+    w = {n: inputs.normal_bf16((d,), 1.0, 76, T, n) for n in range(2)}
+    pos = inputs.rng(78, T).integers(0, 4000, size=T).astype(np.int32)
+    cs = ua.rope_cache(4000, d, 1e6)
+    got = ua.qk_norm_rope(gu.dev(x[0]), gu.dev(x[1]), gu.dev_i32(pos), gu.dev(w[0]), gu.dev(w[1]), cs, eps=1e-6)
+    for n in range(2):
+        bits = oracle.qk_norm_rope(x[n], pos, w[n], 1e-6, cs.cpu().numpy())
+        want, have = oracle.bf16_to_f64(bits), oracle.bf16_to_f64(gu.host_bits(got[n]))
+        pair = np.tile(np.hypot(want[..., :d // 2], want[..., d // 2:]), 2)
+        assert np.all(np.abs(have - want) <= 1.5 * 2.0 ** -7 * pair)
+        assert np.mean(gu.host_bits(got[n]) == bits) > 0.999
+
+
 def test_full_sequence_and_token_wise_rows_are_identical(ua):
     """One call over a whole pack vs one call per decode step (a token of each
     sequence, in shuffled order) and in-place: the same bits for every row."""
