@@ -238,6 +238,10 @@ constexpr int kQTile = kTileKeys;                  // queries per step
 // step, so a unit's tiles come from its XCD's L2 (groups of 4, 16 and 32 were
 // within 2% of 8).
 constexpr int kKeyTileGroup = 8;
+// From this many workgroups to a CU on.  Forward and backward of 24 sequences of
+// 1000 tokens, 16/4 heads, d = 64 (3 to a CU): 383 us single, 440 in eights; 16 of
+// 200-2048, 32/8 heads, d = 128 (5): 785 us in eights.
+constexpr int kKeyTileRounds = 4;
 
 // One matrix phase: acc[db][nb] += T^T w over the 64 rows of the tile at
 // `tr_tile` (kPrev), then s[qb][nb] = R x over the rows of the tile at `row_tile`
@@ -530,6 +534,7 @@ constexpr int kDqNB = 2;
 constexpr int kDqWaveRows = kDqNB * kQCols;
 constexpr int kDqRows = kDqWaves * kDqWaveRows;
 constexpr int kDqTileGroup = 2;  // query tiles (of all the group's heads) to a work unit, see xcd_unit
+constexpr int kDqTileRounds = 8;  // as kKeyTileRounds: that pack with single tiles (11 to a CU) 860 us
 
 template <int D>
 struct DqSmem {
@@ -722,11 +727,13 @@ hipError_t launch_backward_d(const BwdParams& p0, int max_seqlen, hipStream_t st
   BwdParams p = p0;
   const int64_t ktiles = (static_cast<int64_t>(max_seqlen) + kKeyTile - 1) / kKeyTile;
   const int64_t streams = static_cast<int64_t>(p.num_seqs) * p.hkv;
-  p.kt_group = unit_tiles(streams, kKeyTileGroup);
-  p.qt_group = unit_tiles(streams, kDqTileGroup);
+  const int64_t qtiles = (static_cast<int64_t>(max_seqlen) + kDqRows - 1) / kDqRows;
+  p.kt_group = unit_tiles(ktiles, busy_workgroups(max_seqlen, p.num_seqs, p.total, kKeyTile, p.hkv), kKeyTileRounds,
+                          kKeyTileGroup);
+  p.qt_group = unit_tiles(qtiles, busy_workgroups(max_seqlen, p.num_seqs, p.total, kDqRows, p.hq), kDqTileRounds,
+                          kDqTileGroup);
   const int64_t kv_units = (ktiles + p.kt_group - 1) / p.kt_group * streams;
   const int64_t nkv = xcd_grid(kv_units, p.kt_group);
-  const int64_t qtiles = (static_cast<int64_t>(max_seqlen) + kDqRows - 1) / kDqRows;
   const int64_t dq_units = (qtiles + p.qt_group - 1) / p.qt_group * streams;
   const int64_t ndq = xcd_grid(dq_units, p.qt_group * p.group);
   if (nprep > 0x7FFFFFFF || nkv > 0x7FFFFFFF || ndq > 0x7FFFFFFF) return hipErrorInvalidConfiguration;

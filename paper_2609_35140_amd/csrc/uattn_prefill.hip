@@ -63,6 +63,9 @@ struct PrefillParams {
 // 16 sequences of 512-8192 tokens, 40/8 heads: 4.59 ms one tile at a time, 4.42
 // two, 4.27-4.37 four, 4.25-4.30 eight; 32/8 heads and 32K tokens within 1%.
 constexpr int kTileGroup = 4;
+// From this many workgroups to a CU on: 9 sequences of 352-5633 tokens, 8/1 heads
+// (3 to a CU), 188 us one tile at a time, 220 four.
+constexpr int kTileRounds = 8;
 
 // Byte offset, from the address of the wave's first row, of the 16-byte
 // piece this lane fetches in the first load instruction of a K (V) tile.
@@ -630,8 +633,7 @@ hipError_t launch_prefill(const PrefillLaunch& a, hipStream_t stream) {
   const int64_t cus = device_cus();
   auto tiles = [&](int64_t rows) { return (static_cast<int64_t>(a.max_seqlen) + rows - 1) / rows; };
   auto busy = [&](int64_t rows) {
-    const int64_t padded = tiles(rows) * a.num_seqs, packed = a.total_tokens / rows + a.num_seqs;
-    return (padded < packed ? padded : packed) * a.num_q_heads;
+    return busy_workgroups(a.max_seqlen, a.num_seqs, a.total_tokens, rows, a.num_q_heads);
   };
   // The split kernel halves a workgroup's chain of tiles and doubles the
   // workgroups, each with some 5 us of its own, so it pays while those fit the
@@ -643,7 +645,7 @@ hipError_t launch_prefill(const PrefillLaunch& a, hipStream_t stream) {
   const bool split = a.max_seqlen <= kSplitRows || busy(kSplitRows) <= cus ||
                      (busy(kWgRows) <= cus && a.max_seqlen > 2 * kChunkKeys);
   const int64_t units = static_cast<int64_t>(a.num_seqs) * a.num_kv_heads;
-  p.tile_group = split ? 1 : unit_tiles(units, kTileGroup);
+  p.tile_group = split ? 1 : unit_tiles(tiles(kWgRows), busy(kWgRows), kTileRounds, kTileGroup);
   const int64_t ngroups = (tiles(split ? kSplitRows : kWgRows) + p.tile_group - 1) / p.tile_group * units;
   const int64_t nblocks = xcd_grid(ngroups, p.group * p.tile_group);
   if (nblocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;

@@ -34,10 +34,21 @@ __device__ __forceinline__ XcdUnit xcd_unit(int pid, int members) {
   const int j = pid / kXcds;
   return {j / members * kXcds + pid % kXcds, j % members};
 }
-// Tiles of a stream (a sequence's kv head) to a unit: `most`, or 1 where a
-// launch has fewer streams than XCDs, whose longest tiles would otherwise
-// all land on the first ones.
-inline int unit_tiles(int64_t streams, int most) { return streams >= kXcds ? most : 1; }
+// Workgroups with rows in them, at most, of a launch that cuts every sequence
+// (max_seqlen at most, total_tokens together) into tiles of `rows` rows, for
+// each of `heads` heads.
+inline int64_t busy_workgroups(int64_t max_seqlen, int64_t num_seqs, int64_t total_tokens, int64_t rows, int64_t heads) {
+  const int64_t padded = (max_seqlen + rows - 1) / rows * num_seqs, packed = total_tokens / rows + num_seqs;
+  return (padded < packed ? padded : packed) * heads;
+}
+// Tiles of a stream (a sequence's kv head) to a unit: up to `most` where the
+// launch keeps every CU busy for at least `rounds` workgroups.  With fewer, the
+// XCDs that get one unit more than the others, or the longest sequence's,
+// finish well after them.
+inline int unit_tiles(int64_t tiles, int64_t busy, int rounds, int most) {
+  if (busy < static_cast<int64_t>(rounds) * device_cus()) return 1;
+  return static_cast<int>(tiles < most ? tiles : most);
+}
 // Workgroups of a launch over `units` units (ids past the last unit do nothing).
 inline int64_t xcd_grid(int64_t units, int64_t members) { return (units + kXcds - 1) / kXcds * kXcds * members; }
 
