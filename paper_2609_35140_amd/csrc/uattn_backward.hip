@@ -238,9 +238,10 @@ constexpr int kQTile = kTileKeys;                  // queries per step
 // step, so a unit's tiles come from its XCD's L2 (groups of 4, 16 and 32 were
 // within 2% of 8).
 constexpr int kKeyTileGroup = 8;
-// From this many workgroups to a CU on.  Forward and backward of 24 sequences of
-// 1000 tokens, 16/4 heads, d = 64 (3 to a CU): 383 us single, 440 in eights; 16 of
-// 200-2048, 32/8 heads, d = 128 (5): 785 us in eights.
+// From this many workgroups to a CU on.  Below, forward and backward of equal
+// lengths lose by it (single tiles / eights, us: 24 of 1000, 16/4 heads, d = 64
+// 383 / 440; 10 of 1000, 32/8 heads, d = 128 485 / 511), though ragged packs may
+// still gain (16 of 200-2048, 32/8 heads 859 / 796).
 constexpr int kKeyTileRounds = 4;
 
 // One matrix phase: acc[db][nb] += T^T w over the 64 rows of the tile at
@@ -534,7 +535,7 @@ constexpr int kDqNB = 2;
 constexpr int kDqWaveRows = kDqNB * kQCols;
 constexpr int kDqRows = kDqWaves * kDqWaveRows;
 constexpr int kDqTileGroup = 2;  // query tiles (of all the group's heads) to a work unit, see xcd_unit
-constexpr int kDqTileRounds = 8;  // as kKeyTileRounds: that pack with single tiles (11 to a CU) 860 us
+constexpr int kDqTileRounds = 8;  // the forward's line (kTileRounds); not measured apart
 
 template <int D>
 struct DqSmem {
