@@ -379,7 +379,7 @@ def main():
             "avg_launch_ms": round(ph["upd"], 4),
         },
         "roofline_backward": {
-            "kernel": f"uattn_prefill_backward (bwd_prep + bwd_dkdv + bwd_dq over {B} x {L})",
+            "kernel": f"uattn_prefill_backward (bwd_prep + bwd_grads over {B} x {L})",
             "bound": "mfma",
             "achieved": round(tf(bwd_flop, ph["bwd"]), 2),
             "peak": BF16_PEAK_TFLOPS,
