@@ -150,6 +150,7 @@ struct BwdParams {
   // work units of the two kernels (see xcd_unit), and the key or query tiles to one
   int kv_units, dq_units, kt_group, qt_group;
   int kv_blocks;  // bwd_grads_kernel: the workgroups before the dQ ones
+  int first;      // workgroups of the launches before this one
   float c, scale;
 };
 
@@ -171,7 +172,7 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(BwdParams p) {
   constexpr int LPR = D / 8;
   constexpr int kRows = 256 / LPR;
   const int64_t rows = static_cast<int64_t>(p.total) * p.hq;
-  const int64_t r = static_cast<int64_t>(blockIdx.x) * kRows + threadIdx.x / LPR;
+  const int64_t r = static_cast<int64_t>(p.first + blockIdx.x) * kRows + threadIdx.x / LPR;
   const int sub = threadIdx.x % LPR;
   int64_t row = 0;  // token-major index of (t, h) in out, dout and lse
   float acc = 0.f;
@@ -713,7 +714,7 @@ __global__ __launch_bounds__(kKvWaves * 64, 1) void bwd_grads_kernel(BwdParams p
     DqSmem<D> dq;
   };
   __shared__ __attribute__((aligned(1024))) Smem sm;
-  const int pid = blockIdx.x;
+  const int pid = p.first + blockIdx.x;
   if (pid < p.kv_blocks)
     bwd_dkdv<D>(p, sm.dkdv, pid);
   else
@@ -737,25 +738,19 @@ hipError_t launch_backward_d(const BwdParams& p0, int max_seqlen, hipStream_t st
   const int64_t nkv = xcd_grid(kv_units, p.kt_group);
   const int64_t dq_units = (qtiles + p.qt_group - 1) / p.qt_group * streams;
   const int64_t ndq = xcd_grid(dq_units, p.qt_group * p.group);
-  if (nprep > 0x7FFFFFFF || nkv > 0x7FFFFFFF || ndq > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+  if (nkv + ndq > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
   p.kv_units = static_cast<int>(kv_units);
   p.dq_units = static_cast<int>(dq_units);
   p.kv_blocks = static_cast<int>(nkv);
-  hipLaunchKernelGGL(bwd_prep_kernel<D>, dim3(static_cast<unsigned>(nprep)), dim3(256), 0, stream, p);
-  hipError_t e = hipGetLastError();
+  const hipError_t e = launch_parts(nprep, 256, [&](int first, unsigned n) {
+    p.first = first;
+    hipLaunchKernelGGL(bwd_prep_kernel<D>, dim3(n), dim3(256), 0, stream, p);
+  });
   if (e != hipSuccess) return e;
-  const dim3 block(kKvWaves * 64);
-  if (nkv + ndq < (int64_t{1} << 32) / (kKvWaves * 64)) {
-    hipLaunchKernelGGL(bwd_grads_kernel<D>, dim3(static_cast<unsigned>(nkv + ndq)), block, 0, stream, p);
-    return hipGetLastError();
-  }
-  // more threads than one grid takes
-  hipLaunchKernelGGL(bwd_grads_kernel<D>, dim3(static_cast<unsigned>(nkv)), block, 0, stream, p);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  p.kv_blocks = 0;
-  hipLaunchKernelGGL(bwd_grads_kernel<D>, dim3(static_cast<unsigned>(ndq)), block, 0, stream, p);
-  return hipGetLastError();
+  return launch_parts(nkv + ndq, kKvWaves * 64, [&](int first, unsigned n) {
+    p.first = first;
+    hipLaunchKernelGGL(bwd_grads_kernel<D>, dim3(n), dim3(kKvWaves * 64), 0, stream, p);
+  });
 }
 
 }  // namespace

@@ -62,6 +62,7 @@ struct DecodeParams {
   int32_t* ws_cnt;   // [batch][Hkv] arrival counters, zero between calls
   int batch, hq, hkv, group, maxp, page_size, page_shift, num_pages, max_seqlen, nchunk_max;
   int nslot;         // partial slots per (entry, q head): nchunk_max rounded up to even
+  int first;         // decode_merge_kernel: workgroups of the launches before this one
   float c;
 };
 
@@ -200,7 +201,7 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(DecodeParams p) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nrows = p.batch * p.hq;
-  const int row0 = blockIdx.x * R;
+  const int row0 = (p.first + blockIdx.x) * R;
   const char* zero = reinterpret_cast<const char*>(g_zero_rows) + 16 * (lane & 15);
   // chunk counts of the workgroup's rows (0 past the last row and for
   // one-chunk entries, whose outputs the walk wrote)
@@ -907,27 +908,23 @@ hipError_t launch_decode(const DecodeLaunch& a, hipStream_t stream) {
     if constexpr (kBuf) {
       constexpr int kRows = 256 / kD;
       const int64_t rows = static_cast<int64_t>(a.batch) * a.num_q_heads;
-      hipLaunchKernelGGL(decode_merge_kernel<kD>, dim3(static_cast<unsigned>((rows + kRows - 1) / kRows)), dim3(256), 0,
-                         stream, p);
+      if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+      return launch_parts((rows + kRows - 1) / kRows, 256, [&](int first, unsigned n) {
+        p.first = first;
+        hipLaunchKernelGGL(decode_merge_kernel<kD>, dim3(n), dim3(256), 0, stream, p);
+      });
     }
+    return hipGetLastError();
   };
   auto pick_d = [&](auto d_const) {
     auto pick_nb = [&](auto nb_const) {
       if (buffered)
-        pick(d_const, nb_const, std::true_type{});
-      else
-        pick(d_const, nb_const, std::false_type{});
+        return pick(d_const, nb_const, std::true_type{});
+      return pick(d_const, nb_const, std::false_type{});
     };
-    if (two)
-      pick_nb(std::integral_constant<int, 2>{});
-    else
-      pick_nb(std::integral_constant<int, 1>{});
+    return two ? pick_nb(std::integral_constant<int, 2>{}) : pick_nb(std::integral_constant<int, 1>{});
   };
-  if (a.head_dim == 128)
-    pick_d(std::integral_constant<int, 128>{});
-  else
-    pick_d(std::integral_constant<int, 64>{});
-  return hipGetLastError();
+  return a.head_dim == 128 ? pick_d(std::integral_constant<int, 128>{}) : pick_d(std::integral_constant<int, 64>{});
 }
 
 }  // namespace uattn

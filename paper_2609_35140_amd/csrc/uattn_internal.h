@@ -126,6 +126,21 @@ struct BackwardLaunch {
 hipError_t launch_backward(const BackwardLaunch& a, hipStream_t stream);
 size_t backward_ws_bytes(int64_t total_tokens, int64_t num_q_heads);
 
+// A grid holds fewer than 2^32 threads: past that it starts modulo 2^32, the rest
+// is never run and no error is reported.  Calls launch(first, n) for consecutive
+// runs of workgroups that fit, each cut at a multiple of the XCD count.
+template <class Launch>
+hipError_t launch_parts(int64_t workgroups, int threads, const Launch& launch) {
+  if (workgroups > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+  const int64_t most = ((int64_t{1} << 32) / threads - 1) / 8 * 8;
+  for (int64_t first = 0; first < workgroups; first += most) {
+    launch(static_cast<int>(first), static_cast<unsigned>(workgroups - first < most ? workgroups - first : most));
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // Compute units of the current device (cached per device; 256 if the query fails).
 int32_t device_cus();
 

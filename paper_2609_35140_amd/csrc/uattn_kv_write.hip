@@ -25,8 +25,9 @@ struct KvWriteParams {
   int32_t num_tokens, batch, maxp, page_size, num_pages, hkv, pieces;  // pieces = head_dim / 8
 };
 
-// One workgroup per token; its threads copy the token's 16-byte pieces
-// (heads x pieces per head), all from one workgroup-uniform destination page.
+// One workgroup per token (several tokens to one past the largest grid); its
+// threads copy the token's 16-byte pieces (heads x pieces per head), all from one
+// workgroup-uniform destination page.
 __global__ __launch_bounds__(256) void kv_write_kernel(KvWriteParams p) {
   const int per_token = p.hkv * p.pieces;
   for (int64_t n = blockIdx.x; n < p.num_tokens; n += gridDim.x) {
@@ -73,7 +74,8 @@ hipError_t launch_kv_write(const KvWriteLaunch& a, hipStream_t stream) {
   // one workgroup per token, sized to its pieces (a multiple of the wave)
   const int per_token = a.num_kv_heads * p.pieces;
   const int threads = per_token >= 256 ? 256 : (per_token + 63) / 64 * 64;
-  const dim3 grid(static_cast<unsigned>(a.num_tokens));
+  const int most = (1 << 22) - 1;  // fewer than 2^32 threads
+  const dim3 grid(static_cast<unsigned>(a.num_tokens < most ? a.num_tokens : most));
   const dim3 block(static_cast<unsigned>(threads));
   hipLaunchKernelGGL(kv_write_kernel, grid, block, 0, stream, p);
   return hipGetLastError();

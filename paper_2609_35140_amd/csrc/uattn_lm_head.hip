@@ -42,6 +42,7 @@ struct LmHeadParams {
   __bf16* out;          // logits, or nullptr (fused log-prob without stored logits)
   int64_t hs, ws, os;
   int32_t T, V, K, n_vt, n_tt;
+  int32_t first;        // workgroups of the launches before this one
   // fused log-prob epilogue
   const int32_t* targets;
   float* part_m;        // [n_vt][T] tile max of the raw bf16 logits
@@ -268,7 +269,7 @@ __device__ __forceinline__ void lm_head_tile(const LmHeadParams& p, typename LmC
 template <int VT, int TT, int WM, int WN, int STAGES, int kKC, bool kLogprob>
 __global__ __launch_bounds__(WM * WN * 64, 1) void lm_head_kernel(LmHeadParams p) {
   __shared__ __attribute__((aligned(1024))) typename LmCfg<VT, TT, WM, WN, STAGES, kKC>::Smem sm;
-  const int pid = blockIdx.x;
+  const int pid = p.first + blockIdx.x;
   const int xcd = pid % kLmXcds, kk = pid / kLmXcds;
   const int vt = xcd + kLmXcds * (kk / p.n_tt);
   const int tt = kk % p.n_tt;
@@ -301,7 +302,8 @@ __global__ __launch_bounds__(512, 1) void lm_head_wide_kernel(LmHeadParams p) {
   constexpr int BI = kWideVT / kWideWM / 16, BJ = kWideTT / kWideWN / 16;  // 4 x 8 blocks of 16 x 16
   constexpr int kStage = (kWideVT + kWideTT) * kWideKC;                  // elements: weight rows, then hidden rows
   __shared__ __attribute__((aligned(1024))) __bf16 sm[2 * kStage];
-  const int xcd = blockIdx.x % kLmXcds, kk = blockIdx.x / kLmXcds;
+  const int pid = p.first + blockIdx.x;
+  const int xcd = pid % kLmXcds, kk = pid / kLmXcds;
   const int vt = xcd + kLmXcds * (kk / p.n_tt);
   const int tt = kk % p.n_tt;
   if (vt >= p.n_vt) return;
@@ -446,10 +448,11 @@ __global__ __launch_bounds__(256) void logprob_fold_kernel(const float* __restri
                                                            const float* __restrict__ part_s,
                                                            const float* __restrict__ y_logit,
                                                            const int32_t* __restrict__ targets, int32_t T, int32_t V,
-                                                           int32_t n_vt, float it, float k, float* __restrict__ logp) {
+                                                           int32_t n_vt, float it, float k, int32_t first_wg,
+                                                           float* __restrict__ logp) {
   __shared__ float2 run[kFoldSegs][kFoldTokens];
   const int tok = threadIdx.x % kFoldTokens, seg = threadIdx.x / kFoldTokens;
-  const int t = blockIdx.x * kFoldTokens + tok;
+  const int t = (first_wg + blockIdx.x) * kFoldTokens + tok;
   const int len = (n_vt + kFoldSegs - 1) / kFoldSegs;
   const int first = seg * len, last = min(first + len, n_vt);
   float M = 0.f, S = 0.f;
@@ -495,10 +498,10 @@ hipError_t launch_cfg(LmHeadParams p, hipStream_t stream) {
   p.n_vt = (p.V + VT - 1) / VT;
   p.n_tt = (p.T + TT - 1) / TT;
   const int64_t nblocks = static_cast<int64_t>((p.n_vt + kLmXcds - 1) / kLmXcds) * kLmXcds * p.n_tt;
-  if (nblocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL((lm_head_kernel<VT, TT, WM, WN, STAGES, kKC, kLogprob>), dim3(static_cast<unsigned>(nblocks)),
-                     dim3(WM * WN * 64), 0, stream, p);
-  return hipGetLastError();
+  return launch_parts(nblocks, WM * WN * 64, [&](int first, unsigned n) {
+    p.first = first;
+    hipLaunchKernelGGL((lm_head_kernel<VT, TT, WM, WN, STAGES, kKC, kLogprob>), dim3(n), dim3(WM * WN * 64), 0, stream, p);
+  });
 }
 
 template <bool kLogprob>
@@ -506,9 +509,10 @@ hipError_t launch_wide(LmHeadParams p, hipStream_t stream) {
   p.n_vt = (p.V + kWideVT - 1) / kWideVT;
   p.n_tt = (p.T + kWideTT - 1) / kWideTT;
   const int64_t nblocks = static_cast<int64_t>((p.n_vt + kLmXcds - 1) / kLmXcds) * kLmXcds * p.n_tt;
-  if (nblocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL(lm_head_wide_kernel<kLogprob>, dim3(static_cast<unsigned>(nblocks)), dim3(512), 0, stream, p);
-  return hipGetLastError();
+  return launch_parts(nblocks, 512, [&](int first, unsigned n) {
+    p.first = first;
+    hipLaunchKernelGGL(lm_head_wide_kernel<kLogprob>, dim3(n), dim3(512), 0, stream, p);
+  });
 }
 
 // Tile shape by the number of rows.  Every shape adds the same products in the
@@ -586,9 +590,11 @@ hipError_t launch_lm_head_logprob(const LmHeadLaunch& a, const int32_t* targets,
   p.k = static_cast<float>(static_cast<double>(inv_temperature) * 1.4426950408889634);
   hipError_t e = launch_rows<true>(p, stream);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(logprob_fold_kernel, dim3((a.num_rows + kFoldTokens - 1) / kFoldTokens), dim3(256), 0, stream, p.part_m, p.part_s,
-                     p.y_logit, targets, a.num_rows, a.vocab, static_cast<int32_t>(n_vt), inv_temperature, p.k, logp);
-  return hipGetLastError();
+  const int64_t folds = (static_cast<int64_t>(a.num_rows) + kFoldTokens - 1) / kFoldTokens;
+  return launch_parts(folds, 256, [&](int first, unsigned n) {
+    hipLaunchKernelGGL(logprob_fold_kernel, dim3(n), dim3(256), 0, stream, p.part_m, p.part_s, p.y_logit, targets,
+                       a.num_rows, a.vocab, static_cast<int32_t>(n_vt), inv_temperature, p.k, first, logp);
+  });
 }
 
 }  // namespace uattn

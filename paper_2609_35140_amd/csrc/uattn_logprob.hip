@@ -49,8 +49,8 @@ __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w 
 
 __global__ __launch_bounds__(kThreads) void logprob_kernel(const uint16_t* __restrict__ logits, int64_t stride,
                                                            const int32_t* __restrict__ targets, int vocab, float it,
-                                                           float k, float* __restrict__ logp) {
-  const int row = blockIdx.x, tid = threadIdx.x;
+                                                           float k, int first, float* __restrict__ logp) {
+  const int row = first + blockIdx.x, tid = threadIdx.x;
   const uint16_t* x = logits + static_cast<int64_t>(row) * stride;
   MaxSum acc{neg_inf(), 0.f};
   const int nvec = vocab / 8;
@@ -114,10 +114,10 @@ __global__ __launch_bounds__(kThreads) void logprob_kernel(const uint16_t* __res
 
 hipError_t launch_logprob(const LogprobLaunch& a, hipStream_t stream) {
   const float k = static_cast<float>(static_cast<double>(a.inv_temperature) * 1.4426950408889634);
-  hipLaunchKernelGGL(logprob_kernel, dim3(a.num_rows), dim3(kThreads), 0, stream,
-                     static_cast<const uint16_t*>(a.logits), a.row_stride, a.targets, a.vocab, a.inv_temperature, k,
-                     a.logp);
-  return hipGetLastError();
+  return launch_parts(a.num_rows, kThreads, [&](int first, unsigned n) {
+    hipLaunchKernelGGL(logprob_kernel, dim3(n), dim3(kThreads), 0, stream, static_cast<const uint16_t*>(a.logits),
+                       a.row_stride, a.targets, a.vocab, a.inv_temperature, k, first, a.logp);
+  });
 }
 
 }  // namespace uattn

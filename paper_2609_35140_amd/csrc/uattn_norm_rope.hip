@@ -28,6 +28,7 @@ struct NormRopeParams {
   __bf16* k_out;
   float eps;
   int32_t max_position, num_tokens, hq, hkv;
+  int32_t first;  // tokens of the launches before this one
 };
 
 // DPP: lanes exchange values within 16 without an LDS round trip.  Every lane
@@ -104,7 +105,7 @@ __global__ __launch_bounds__(kNormWaves * 64) void qk_norm_rope_kernel(NormRopeP
   const int j = lane % LPR;           // 16-byte piece of the row
   const bool first = j < HALF;
   const int i0 = 8 * (first ? j : j - HALF);  // rotary index of element 0 of this lane
-  const int64_t t = blockIdx.x;
+  const int64_t t = p.first + blockIdx.x;
   const int q_items = (p.hq + RPI - 1) / RPI, items = q_items + (p.hkv + RPI - 1) / RPI;
   if (wave >= items) return;
   const int32_t pos = p.positions[t];
@@ -230,13 +231,14 @@ hipError_t launch_qk_norm_rope(const NormRopeLaunch& a, hipStream_t stream) {
   p.num_tokens = a.num_tokens;
   p.hq = a.num_q_heads;
   p.hkv = a.num_kv_heads;
-  const dim3 grid(static_cast<unsigned>(a.num_tokens));  // one workgroup per token
-  const dim3 block(kNormWaves * 64);
-  if (a.head_dim == 128)
-    hipLaunchKernelGGL(qk_norm_rope_kernel<128>, grid, block, 0, stream, p);
-  else
-    hipLaunchKernelGGL(qk_norm_rope_kernel<64>, grid, block, 0, stream, p);
-  return hipGetLastError();
+  // one workgroup per token
+  return launch_parts(a.num_tokens, kNormWaves * 64, [&](int first, unsigned n) {
+    p.first = first;
+    if (a.head_dim == 128)
+      hipLaunchKernelGGL(qk_norm_rope_kernel<128>, dim3(n), dim3(kNormWaves * 64), 0, stream, p);
+    else
+      hipLaunchKernelGGL(qk_norm_rope_kernel<64>, dim3(n), dim3(kNormWaves * 64), 0, stream, p);
+  });
 }
 
 hipError_t launch_rope_cache(float* cos_sin, int32_t max_position, int32_t head_dim, double theta, hipStream_t stream) {

@@ -53,6 +53,7 @@ struct PrefillParams {
   int hq, hkv, group, total;
   int num_seqs, ngroups;  // work groups = (tile_group query tiles from the end, sequence, kv head)
   int tile_group;         // query tiles to a work group
+  int first;              // workgroups of the launches before this one
   float c;
 };
 
@@ -218,7 +219,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void prefill_kernel(PrefillParams p
   using TL = TileLayout<D>;
   __shared__ __attribute__((aligned(1024))) __bf16 lds[2 * TL::kStageElems];
 
-  const XcdUnit unit = xcd_unit(blockIdx.x, p.tile_group * p.group);
+  const XcdUnit unit = xcd_unit(p.first + blockIdx.x, p.tile_group * p.group);
   if (unit.unit >= p.ngroups) return;
   const int zrev = unit.unit / (p.num_seqs * p.hkv) * p.tile_group + unit.member / p.group;
   const int seq = (unit.unit / p.hkv) % p.num_seqs;
@@ -437,7 +438,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void prefill_split_kernel(PrefillPa
   __shared__ float2 part_ml[2][kSplitRowGroups][kNB][kQCols];
   static_assert(kSplitRowGroups * kNB * NDH * 64 * 16 <= TL::kStageElems * 2, "a stream's half partials fit its stage");
 
-  const XcdUnit unit = xcd_unit(blockIdx.x, p.group);
+  const XcdUnit unit = xcd_unit(p.first + blockIdx.x, p.group);
   if (unit.unit >= p.ngroups) return;
   const int zrev = unit.unit / (p.num_seqs * p.hkv);
   const int seq = (unit.unit / p.hkv) % p.num_seqs;
@@ -650,17 +651,18 @@ hipError_t launch_prefill(const PrefillLaunch& a, hipStream_t stream) {
   const int64_t nblocks = xcd_grid(ngroups, p.group * p.tile_group);
   if (nblocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
   p.ngroups = static_cast<int>(ngroups);
-  const dim3 grid(static_cast<unsigned>(nblocks));
-  const dim3 block(kWaves * 64);
-  if (split && a.head_dim == 128)
-    hipLaunchKernelGGL(prefill_split_kernel<128>, grid, block, 0, stream, p);
-  else if (split)
-    hipLaunchKernelGGL(prefill_split_kernel<64>, grid, block, 0, stream, p);
-  else if (a.head_dim == 128)
-    hipLaunchKernelGGL(prefill_kernel<128>, grid, block, 0, stream, p);
-  else
-    hipLaunchKernelGGL(prefill_kernel<64>, grid, block, 0, stream, p);
-  return hipGetLastError();
+  return launch_parts(nblocks, kWaves * 64, [&](int first, unsigned n) {
+    p.first = first;
+    const dim3 grid(n), block(kWaves * 64);
+    if (split && a.head_dim == 128)
+      hipLaunchKernelGGL(prefill_split_kernel<128>, grid, block, 0, stream, p);
+    else if (split)
+      hipLaunchKernelGGL(prefill_split_kernel<64>, grid, block, 0, stream, p);
+    else if (a.head_dim == 128)
+      hipLaunchKernelGGL(prefill_kernel<128>, grid, block, 0, stream, p);
+    else
+      hipLaunchKernelGGL(prefill_kernel<64>, grid, block, 0, stream, p);
+  });
 }
 
 }  // namespace uattn

@@ -435,3 +435,20 @@ def test_short_calls_give_the_bits_of_large_ones(ua, hq, hkv, d):
         out, lse = ua.prefill(q[rows], k[rows], v[rows], gu.dev_i32([0, n]), n, return_lse=True)
         assert torch.equal(out.view(torch.int16), full[rows].view(torch.int16)), n
         assert torch.equal(lse.view(torch.int32), full_lse[rows].view(torch.int32)), n
+
+
+@pytest.mark.parametrize("n", [40000, 60000])
+def test_more_workgroups_than_one_grid(ua, n):
+    """Mostly empty sequences, 32 heads and tiles for 1280 keys: 10 and 15 million workgroups of 512 threads in units of four
+    tiles (6 and 10 million without), past the 2^32 threads of one grid.  Every row equals the few sequences alone."""
+    import torch
+    lens = [300, 1280, 1, 129, 640]
+    T, h, d = sum(lens), 32, 64
+    q, k, v = (inputs.normal_bf16_device((T, h, d), 1.0, 84, i) for i in range(3))
+    want, want_lse = ua.prefill(q, k, v, gu.dev_i32(inputs.cu_seqlens(lens)), 1280, return_lse=True)
+    spread = np.zeros(n, dtype=np.int64)
+    spread[[7, n // 3, n // 2, n - 2000, n - 1]] = lens
+    out, lse = torch.full_like(want, 7.0), torch.full_like(want_lse, 7.0)
+    ua.prefill(q, k, v, gu.dev_i32(inputs.cu_seqlens(spread)), 1280, out=out, return_lse=True, lse=lse)
+    assert torch.equal(out.view(torch.int16), want.view(torch.int16))
+    assert torch.equal(lse.view(torch.int32), want_lse.view(torch.int32))

@@ -102,6 +102,42 @@ def test_tile_edges_match_oracle(ua, lens, hq, hkv, d, sigma):
     test_matches_oracle(ua, lens, hq, hkv, d, sigma)
 
 
+def test_more_workgroups_than_one_grid(ua):
+    """30,000 sequences, all but four empty, 32 kv heads and tiles for 1280 keys: 9.6 million dK/dV workgroups of 512
+    threads, past the 2^32 threads of one grid.  The same bits as the four alone."""
+    import torch
+    lens = [300, 1280, 1, 129]
+    q, k, v, do, cu = _inputs(lens, 32, 32, 64, 1.0, 5)
+    q, k, v, do = (gu.dev(x) for x in (q, k, v, do))
+    few = gu.dev_i32(cu)
+    out, lse = ua.prefill(q, k, v, few, 1280, return_lse=True)
+    want = ua.prefill_backward(q, k, v, out, do, lse, few, 1280)
+    spread = np.zeros(30000, dtype=np.int64)
+    spread[[7, 12345, 20000, 29999]] = lens
+    got = ua.prefill_backward(q, k, v, out, do, lse, gu.dev_i32(inputs.cu_seqlens(spread)), 1280)
+    for a, b in zip(got, want):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+@pytest.mark.parametrize("n", [26000, 60000])
+def test_more_workgroups_than_one_grid(ua, n):
+    """Mostly empty sequences, 32 kv heads and tiles for 1280 keys: 8.3 and 19 million dK/dV workgroups of 512 threads (more
+    in units of tiles), past the 2^32 threads of one grid.  Every gradient equals the one of the few sequences alone."""
+    import torch
+    lens = [300, 1280, 1, 129, 640]
+    q, k, v, do, cu = _inputs(lens, 32, 32, 64, 1.0, 5)
+    q, k, v, do = (gu.dev(x) for x in (q, k, v, do))
+    few = gu.dev_i32(cu)
+    out, lse = ua.prefill(q, k, v, few, 1280, return_lse=True)
+    want = ua.prefill_backward(q, k, v, out, do, lse, few, 1280)
+    spread = np.zeros(n, dtype=np.int64)
+    spread[[7, n // 3, n // 2, n - 2000, n - 1]] = lens
+    got = [torch.full_like(x, 7.0) for x in (q, k, v)]
+    ua.prefill_backward(q, k, v, out, do, lse, gu.dev_i32(inputs.cu_seqlens(spread)), 1280, dq=got[0], dk=got[1], dv=got[2])
+    for a, b in zip(got, want):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
 def test_repeated_calls_are_bitwise_equal(ua):
     q, k, v, do, cu = _inputs([700, 333, 64], 8, 2, 128, 1.0, 1)
     first = [gu.host_bits(x) for x in _run(ua, q, k, v, do, cu)]

@@ -104,3 +104,14 @@ def test_logprob_vocab_edges(ua, V):
     # all but one masked: log of one weight exp2(fma(x, k, -fl(x k))), whose exponent is that product's rounding, at
     # most 2^-24 |x k|
     assert abs(got[2]) <= 2.0 ** -24 * abs(m[2]) + 2.0 ** -24
+
+
+@pytest.mark.parametrize("T", [(1 << 22) + 9, (1 << 24), (1 << 24) + 9])
+def test_logprob_more_rows_than_one_grid(ua, T):
+    """Workgroups of 1024 or 256 threads, one to a row: past the 2^32 threads of one grid."""
+    import torch
+    row = gu.dev(inputs.logits_bf16(1, 8, 2.0, tag=8))
+    tg = torch.arange(T, dtype=torch.int32, device="cuda") % 8
+    want = ua.logprob(row.expand(8, 8).contiguous(), tg[:8])
+    got = ua.logprob(row.expand(T, 8).contiguous(), tg, out=torch.full((T,), 7.0, device="cuda"))
+    assert torch.equal(got, want[tg.long()])

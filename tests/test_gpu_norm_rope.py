@@ -120,3 +120,27 @@ def test_position_outside_the_table_gives_nan_rows(ua):
     cs = ua.rope_cache(16, d, 1e4)
     qo, ko = ua.qk_norm_rope(q, k, gu.dev_i32([3, 16, -1]), w, w, cs)
     assert not torch.isnan(qo[0]).any() and torch.isnan(qo[1]).all() and torch.isnan(ko[2]).all()
+
+
+@pytest.mark.parametrize("T", [(1 << 24), (1 << 24) + 9])
+def test_more_tokens_than_one_grid(ua, T):
+    """Workgroups of 256 threads, one to a token: past the 2^32 threads of one grid (norm and rotation, then the write into
+    the cache).  Tokens repeat with a period of 8."""
+    import torch
+    x = inputs.normal_bf16_device((2, 8, 1, 64), 1.0, 85)
+    w = inputs.normal_bf16_device((2, 64), 1.0, 86)
+    cs = ua.rope_cache(8, 64, 1e4)
+    pos = torch.arange(T, dtype=torch.int32, device="cuda") % 8
+    reps = (T + 7) // 8
+    q, k = (y.repeat(reps, 1, 1)[:T].contiguous() for y in x)
+    want = ua.qk_norm_rope(x[0].contiguous(), x[1].contiguous(), pos[:8].contiguous(), w[0].contiguous(), w[1].contiguous(), cs)
+    ua.qk_norm_rope(q, k, pos, w[0].contiguous(), w[1].contiguous(), cs, q_out=q, k_out=k)
+    for got, ref in zip((q, k), want):
+        full = got[:T // 8 * 8].view(-1, 8, 64).view(torch.int16)
+        assert bool((full == ref.view(8, 64).view(torch.int16)).all())
+        assert torch.equal(got[T // 8 * 8:].view(torch.int16), ref[:T % 8].view(torch.int16))
+    pages = torch.zeros((1, 1, 16, 64), dtype=torch.bfloat16, device="cuda")
+    kp, vp = pages.clone(), pages.clone()
+    ua.kv_write(k, q, torch.zeros((1, 1), dtype=torch.int32, device="cuda"), torch.zeros_like(pos), pos, kp, vp)
+    assert torch.equal(kp[0, 0, :8].view(torch.int16), want[1][:, 0].view(torch.int16))
+    assert torch.equal(vp[0, 0, :8].view(torch.int16), want[0][:, 0].view(torch.int16))
