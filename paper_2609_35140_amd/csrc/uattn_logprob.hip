@@ -1,17 +1,19 @@
 // Per-token log-probability: logp = x[y] - logsumexp(x), x = logits * inv_temperature.
 //
-// One workgroup (1024 threads) per row.  Thread t streams the row's 16-byte
-// vectors t, t+1024, t+2048, ... in batches, keeping an online (max, sum) pair;
-// the 1024 pairs are then combined by a fixed butterfly inside each wave and a
-// fixed pairing of the waves.  The reduction structure depends only on vocab,
-// never on the number of rows or a row's position, so a row's result is
-// bit-identical in any batch (the precondition for reusing rollout
-// log-probabilities with ratio exactly 1).
+// One workgroup per row, of 64 to 1024 threads by the vocabulary (launch_logprob).
+// Thread t streams the row's 16-byte vectors t, t+threads, t+2*threads, ... in
+// batches, keeping an online (max, sum) pair; the pairs are then combined by a
+// fixed butterfly inside each wave and a fixed pairing of the waves.  The reduction
+// structure depends only on vocab, never on the number of rows or a row's
+// position, so a row's result is bit-identical in any batch (the precondition for
+// reusing rollout log-probabilities with ratio exactly 1).
 //
 // The temperature is folded into the exponent: with k = inv_temperature *
 // log2(e) and m the row max of the raw logits (inv_temperature > 0),
 //   sum = sum_v exp2(fma(logit_v, k, -m*k)),
 //   logp = (logit_y - m) * inv_temperature - log2(sum) * ln(2).
+#include <type_traits>
+
 #include "uattn_internal.h"
 #include "uattn_numerics.h"
 
@@ -19,13 +21,6 @@
 
 namespace uattn {
 namespace {
-
-// A row is one workgroup's, so few rows (a decode step) leave most CUs idle and
-// what counts is how fast one CU streams: 16 waves with kBatch loads each in
-// flight.  8 rows of 151,936: 35 us with 256 threads and one load in flight, 17.6
-// with 256 x 8, 13.6 with 512 x 5, 12.7 so; 8192 rows 403 -> 391 us (6.4 TB/s).
-constexpr int kThreads = 1024;
-constexpr int kBatch = 5;  // 16-byte loads in flight per thread
 
 struct MaxSum {
   float m, s;
@@ -47,30 +42,39 @@ constexpr u32x4 kNegInfVec = {0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
+// kBatch 16-byte loads in flight per thread; a batch's loads past the row's end are
+// skipped by the wave, and those of its last vector's wave read as -inf.
+template <int kThreads, int kBatch>
 __global__ __launch_bounds__(kThreads) void logprob_kernel(const uint16_t* __restrict__ logits, int64_t stride,
                                                            const int32_t* __restrict__ targets, int vocab, float it,
                                                            float k, int first, float* __restrict__ logp) {
-  const int row = first + blockIdx.x, tid = threadIdx.x;
+  constexpr int kWaves = kThreads / 64;
+  const int row = first + blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint16_t* x = logits + static_cast<int64_t>(row) * stride;
+  const int y = targets[row];
   MaxSum acc{neg_inf(), 0.f};
   const int nvec = vocab / 8;
-  for (int i0 = tid; i0 < nvec; i0 += kBatch * kThreads) {
+  for (int i0 = 64 * wave; i0 < nvec; i0 += kBatch * kThreads) {
     u32x4 w[kBatch];
 #pragma unroll
     for (int b = 0; b < kBatch; ++b) {
-      const int i = i0 + b * kThreads;
-      w[b] = i < nvec ? *reinterpret_cast<const u32x4*>(x + 8 * static_cast<int64_t>(i)) : kNegInfVec;
+      const int i = i0 + b * kThreads + lane;
+      w[b] = kNegInfVec;
+      if (i < nvec) w[b] = *reinterpret_cast<const u32x4*>(x + 8 * static_cast<int64_t>(i));
     }
     float m_new = acc.m;
 #pragma unroll
     for (int b = 0; b < kBatch; ++b)
+      if (i0 + b * kThreads < nvec)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) m_new = fmaxf(m_new, fmaxf(bf16_lo(w[b][j]), bf16_hi(w[b][j])));
+        for (int j = 0; j < 4; ++j) m_new = fmaxf(m_new, fmaxf(bf16_lo(w[b][j]), bf16_hi(w[b][j])));
     // entries of -inf (a masked vocabulary) add nothing, also where all so far are -inf
     const float mk = m_new == neg_inf() ? 0.f : m_new * k;
     float sum = 0.f;
 #pragma unroll
     for (int b = 0; b < kBatch; ++b) {
+      if (i0 + b * kThreads >= nvec) break;
       float e[8];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -90,17 +94,22 @@ __global__ __launch_bounds__(kThreads) void logprob_kernel(const uint16_t* __res
     MaxSum o{__shfl_xor(acc.m, off, 64), __shfl_xor(acc.s, off, 64)};
     acc = combine(acc, o, k);
   }
-  __shared__ MaxSum part[kThreads / 64];
-  if ((tid & 63) == 0) part[tid >> 6] = acc;
-  __syncthreads();
+  MaxSum part[kWaves];
+  part[0] = acc;
+  if constexpr (kWaves > 1) {
+    __shared__ MaxSum all[kWaves];
+    if (lane == 0) all[wave] = acc;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) part[w] = all[w];
+  }
   if (tid == 0) {
     // the waves' pairs, neighbours first
 #pragma unroll
-    for (int n = 1; n < kThreads / 64; n *= 2)
+    for (int n = 1; n < kWaves; n *= 2)
 #pragma unroll
-      for (int w = 0; w < kThreads / 64; w += 2 * n) part[w] = combine(part[w], part[w + n], k);
+      for (int w = 0; w < kWaves; w += 2 * n) part[w] = combine(part[w], part[w + n], k);
     const MaxSum r = part[0];
-    const int y = targets[row];
     if (y < 0 || y >= vocab) {
       logp[row] = __builtin_nanf("");
     } else {
@@ -112,12 +121,33 @@ __global__ __launch_bounds__(kThreads) void logprob_kernel(const uint16_t* __res
 
 }  // namespace
 
+// Threads to a row by the vocabulary alone (a row's bits do not depend on the
+// number of rows).  Few rows (a decode step) leave most CUs idle, so what counts
+// there is how fast one CU streams a row, many loads in flight; many rows
+// want no idle waves, whose launch and reduction cost as much as a busy one's.  us
+// for 8 and for 8192 rows (vocab 1000 and 2048: 65536), by threads x batch:
+//   1,000     64 x 4   2.7 / 28     256 x 1   2.8 / 63     1024 x 5   3.5 / 283
+//   2,048    128 x 4   2.9 / 52     256 x 4   2.9 / 81      64 x 4    3.1 / 45
+//   16,384   256 x 4   4.0 / 40.7   512 x 5   3.8 / 41.6   1024 x 5   4.3 / 56
+//   50,257   512 x 5   6.2 / 135    256 x 4   7.4 / 142    1024 x 5   6.3 / 147
+//   151,936 1024 x 5  11.5 / 407    512 x 5  12.4 / 412     256 x 1  19 / 424
+// The vectors of a thread stay between one and about sixteen.
 hipError_t launch_logprob(const LogprobLaunch& a, hipStream_t stream) {
   const float k = static_cast<float>(static_cast<double>(a.inv_temperature) * 1.4426950408889634);
-  return launch_parts(a.num_rows, kThreads, [&](int first, unsigned n) {
-    hipLaunchKernelGGL(logprob_kernel, dim3(n), dim3(kThreads), 0, stream, static_cast<const uint16_t*>(a.logits),
-                       a.row_stride, a.targets, a.vocab, a.inv_temperature, k, first, a.logp);
-  });
+  auto launch = [&](auto threads_const, auto batch_const) {
+    constexpr int kThreads = decltype(threads_const)::value, kBatch = decltype(batch_const)::value;
+    return launch_parts(a.num_rows, kThreads, [&](int first, unsigned n) {
+      hipLaunchKernelGGL((logprob_kernel<kThreads, kBatch>), dim3(n), dim3(kThreads), 0, stream,
+                         static_cast<const uint16_t*>(a.logits), a.row_stride, a.targets, a.vocab, a.inv_temperature, k,
+                         first, a.logp);
+    });
+  };
+  using std::integral_constant;
+  if (a.vocab <= 1024) return launch(integral_constant<int, 64>{}, integral_constant<int, 4>{});
+  if (a.vocab <= 2048) return launch(integral_constant<int, 128>{}, integral_constant<int, 4>{});
+  if (a.vocab <= 16384) return launch(integral_constant<int, 256>{}, integral_constant<int, 4>{});
+  if (a.vocab <= 65536) return launch(integral_constant<int, 512>{}, integral_constant<int, 5>{});
+  return launch(integral_constant<int, 1024>{}, integral_constant<int, 5>{});
 }
 
 }  // namespace uattn

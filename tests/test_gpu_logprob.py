@@ -106,9 +106,22 @@ def test_logprob_vocab_edges(ua, V):
     assert abs(got[2]) <= 2.0 ** -24 * abs(m[2]) + 2.0 ** -24
 
 
-@pytest.mark.parametrize("T", [(1 << 22) + 9, (1 << 24), (1 << 24) + 9])
+@pytest.mark.parametrize("V", [512, 520, 1024, 1025, 2048, 2056, 8200, 16384, 16391, 20480, 65536, 65544])
+def test_logprob_block_sizes(ua, V):
+    """The steps of the workgroup's size by the vocabulary, and a full batch of loads and one vector more at each size: the
+    oracle's value (masked rows as above), the same bits in any number of rows."""
+    import torch
+    test_logprob_vocab_edges(ua, V)
+    lg = gu.dev(inputs.logits_bf16(40, V + (-V) % 8, 2.0, tag=V))[:, :V]
+    tg = gu.dev_i32(inputs.targets(40, V, tag=V))
+    full = ua.logprob(lg, tg)
+    for i in range(0, 40, 13):
+        assert torch.equal(ua.logprob(lg[i:i + 1], tg[i:i + 1]), full[i:i + 1])
+
+
+@pytest.mark.parametrize("T", [(1 << 22) + 9, (1 << 24), (1 << 24) + 9, (1 << 26) + 9])
 def test_logprob_more_rows_than_one_grid(ua, T):
-    """Workgroups of 1024 or 256 threads, one to a row: past the 2^32 threads of one grid."""
+    """Workgroups of 1024, 256 or 64 threads, one to a row: past the 2^32 threads of one grid."""
     import torch
     row = gu.dev(inputs.logits_bf16(1, 8, 2.0, tag=8))
     tg = torch.arange(T, dtype=torch.int32, device="cuda") % 8
