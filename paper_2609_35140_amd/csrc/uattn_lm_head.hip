@@ -540,8 +540,15 @@ hipError_t launch_rows(const LmHeadParams& p, hipStream_t stream) {
     if (p.T <= 64 && p.K % 128 == 0) return launch_cfg<64, 64, 4, 1, 2, 128, false>(p, stream);
     if (p.T <= 64) return launch_cfg<64, 64, 4, 1, 2, 64, false>(p, stream);
   }
-  if (p.T <= 128 || p.ws > kWideMaxStride || p.hs > kWideMaxStride)
+  // 128-token tiles: up to 128 rows, and for strides past the wide kernel's 32-bit
+  // offsets while the tiles fit the CUs at once (1024 rows, vocab 4096: 100 us, 122
+  // with 256-token tiles); more of them read the weights too often (260 rows, hidden
+  // stride 2^22 + 8, vocab 32,000: 146 us, 131 with 256; 1024 rows 357, 262).
+  const bool far = p.ws > kWideMaxStride || p.hs > kWideMaxStride;
+  const int64_t tiles128 = static_cast<int64_t>((p.V + kVocabTile - 1) / kVocabTile) * ((p.T + 127) / 128);
+  if (p.T <= 128 || (far && tiles128 <= device_cus()))
     return launch_cfg<kVocabTile, 128, 4, 2, 2, 64, kLogprob>(p, stream);
+  if (far) return launch_cfg<kVocabTile, 256, 4, 2, 2, 64, kLogprob>(p, stream);
   return launch_wide<kLogprob>(p, stream);
 }
 

@@ -98,6 +98,26 @@ def test_tile_shapes_give_the_same_bits(ua, V, H):
         assert torch.equal(stored.view(torch.int16), full[:n].view(torch.int16)), n
 
 
+@pytest.mark.parametrize("which,stride,V", [("hidden", 1 << 22, 300), ("hidden", (1 << 22) + 8, 300),
+                                            ("hidden", (1 << 22) + 8, 25600), ("weight", 1 << 22, 130),
+                                            ("weight", (1 << 22) + 8, 130)])
+def test_far_strides_give_the_same_bits(ua, which, stride, V):
+    """Rows whose distance is the largest that 32-bit byte offsets inside a tile reach, and one step past it (tiles of 128
+    tokens while they fit the GPU at once, else of 256): the bits of contiguous rows, plain and fused."""
+    import torch
+    T, H = 330, 128
+    h = inputs.normal_bf16_device((T, H), 1.0, 99, 1)
+    w = inputs.normal_bf16_device((V, H), 0.25, 99, 2)
+    tg = gu.dev_i32(inputs.targets(T, V, tag=V))
+    want, want_lp = ua.lm_head(h, w), ua.lm_head_logprob(h, w, tg)
+    rows = T if which == "hidden" else V
+    far = torch.empty((rows - 1) * stride + H, dtype=torch.bfloat16, device="cuda").as_strided((rows, H), (stride, 1))
+    far.copy_(h if which == "hidden" else w)
+    h, w = (far, w) if which == "hidden" else (h, far)
+    assert torch.equal(ua.lm_head(h, w).view(torch.int16), want.view(torch.int16))
+    assert torch.equal(ua.lm_head_logprob(h, w, tg).view(torch.int32), want_lp.view(torch.int32))
+
+
 @pytest.mark.parametrize("V", [200, 4096, 4097, 8193])
 def test_fused_logprob_fold_runs(ua, V):
     """1, 16, 17 and 33 vocabulary tiles: runs of one, full and empty runs of the fold."""
