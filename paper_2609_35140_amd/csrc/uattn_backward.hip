@@ -147,8 +147,7 @@ struct BwdParams {
   __bf16* dk;
   __bf16* dv;
   int hq, hkv, group, total, num_seqs;
-  // work units of the two kernels (see xcd_unit), and the key or query tiles to one
-  int kv_units, dq_units, kt_group, qt_group;
+  XcdUnits kv_units, dq_units;  // of key tiles; of query tiles, counted from the end
   int kv_blocks;  // bwd_grads_kernel: the workgroups before the dQ ones
   int first;      // workgroups of the launches before this one
   float c, scale;
@@ -235,7 +234,7 @@ constexpr int kKvWaves = 2 * kKvPairs;
 constexpr int kKeysPerPair = 32;
 constexpr int kKeyTile = kKvPairs * kKeysPerPair;  // keys per workgroup
 constexpr int kQTile = kTileKeys;                  // queries per step
-// Key tiles to a work unit (see xcd_unit): they walk the same query tiles in
+// Key tiles to a work unit (see xcd_tile): they walk the same query tiles in
 // step, so a unit's tiles come from its XCD's L2 (groups of 4, 16 and 32 were
 // within 2% of 8).
 constexpr int kKeyTileGroup = 8;
@@ -343,11 +342,9 @@ __device__ __forceinline__ void bwd_dkdv(const BwdParams& p, DkdvSmem<D>& sm, in
   __bf16* const lds = sm.tiles;
   f32x4(*const pbuf)[8][64] = sm.p;
 
-  const XcdUnit w = xcd_unit(pid, p.kt_group);
-  if (w.unit >= p.kv_units) return;
-  const int kt = w.unit / (p.num_seqs * p.hkv) * p.kt_group + w.member;
-  const int seq = (w.unit / p.hkv) % p.num_seqs;
-  const int kvh = w.unit % p.hkv;
+  const XcdTile at = xcd_tile(pid, p.kv_units);
+  if (at.tile >= p.kv_units.ntiles) return;
+  const int kt = at.tile, seq = at.seq, kvh = at.kvh;
   int lo, L;
   seq_range(p, seq, lo, L);
   const int k0 = kt * kKeyTile;
@@ -535,7 +532,7 @@ constexpr int kDqWaves = 8;
 constexpr int kDqNB = 2;
 constexpr int kDqWaveRows = kDqNB * kQCols;
 constexpr int kDqRows = kDqWaves * kDqWaveRows;
-constexpr int kDqTileGroup = 2;  // query tiles (of all the group's heads) to a work unit, see xcd_unit
+constexpr int kDqTileGroup = 2;  // query tiles (of all the group's heads) to a work unit, see xcd_tile
 constexpr int kDqTileRounds = 8;  // the forward's line (kTileRounds); not measured apart
 
 template <int D>
@@ -552,13 +549,11 @@ __device__ __forceinline__ void bwd_dq(const BwdParams& p, DqSmem<D>& sm, int pi
   constexpr int kStageElems = DqSmem<D>::kStageElems;
   __bf16* const lds = sm.tiles;
 
-  const XcdUnit w = xcd_unit(pid, p.qt_group * p.group);
-  if (w.unit >= p.dq_units) return;
+  const XcdTile at = xcd_tile(pid, p.dq_units);
+  if (at.tile >= p.dq_units.ntiles) return;
   // query tiles counted from the end: longest work first
-  const int zrev = w.unit / (p.num_seqs * p.hkv) * p.qt_group + w.member / p.group;
-  const int seq = (w.unit / p.hkv) % p.num_seqs;
-  const int kvh = w.unit % p.hkv;
-  const int head = kvh * p.group + w.member % p.group;
+  const int zrev = at.tile, seq = at.seq, kvh = at.kvh;
+  const int head = kvh * p.group + at.head;
   int lo, L;
   seq_range(p, seq, lo, L);
   const int nqt = (L + kDqRows - 1) / kDqRows;
@@ -728,19 +723,15 @@ hipError_t launch_backward_d(const BwdParams& p0, int max_seqlen, hipStream_t st
   const int64_t nprep = (rows + kPrepRows - 1) / kPrepRows;
   BwdParams p = p0;
   const int64_t ktiles = (static_cast<int64_t>(max_seqlen) + kKeyTile - 1) / kKeyTile;
-  const int64_t streams = static_cast<int64_t>(p.num_seqs) * p.hkv;
   const int64_t qtiles = (static_cast<int64_t>(max_seqlen) + kDqRows - 1) / kDqRows;
-  p.kt_group = unit_tiles(ktiles, busy_workgroups(max_seqlen, p.num_seqs, p.total, kKeyTile, p.hkv), kKeyTileRounds,
+  const int kt_group = unit_tiles(ktiles, busy_workgroups(max_seqlen, p.num_seqs, p.total, kKeyTile, p.hkv), kKeyTileRounds,
                           kKeyTileGroup);
-  p.qt_group = unit_tiles(qtiles, busy_workgroups(max_seqlen, p.num_seqs, p.total, kDqRows, p.hq), kDqTileRounds,
+  const int qt_group = unit_tiles(qtiles, busy_workgroups(max_seqlen, p.num_seqs, p.total, kDqRows, p.hq), kDqTileRounds,
                           kDqTileGroup);
-  const int64_t kv_units = (ktiles + p.kt_group - 1) / p.kt_group * streams;
-  const int64_t nkv = xcd_grid(kv_units, p.kt_group);
-  const int64_t dq_units = (qtiles + p.qt_group - 1) / p.qt_group * streams;
-  const int64_t ndq = xcd_grid(dq_units, p.qt_group * p.group);
+  p.kv_units = xcd_units(ktiles, kt_group, 1, p.num_seqs, p.hkv);
+  p.dq_units = xcd_units(qtiles, qt_group, p.group, p.num_seqs, p.hkv);
+  const int64_t nkv = xcd_grid(p.kv_units), ndq = xcd_grid(p.dq_units);
   if (nkv + ndq > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
-  p.kv_units = static_cast<int>(kv_units);
-  p.dq_units = static_cast<int>(dq_units);
   p.kv_blocks = static_cast<int>(nkv);
   const hipError_t e = launch_parts(nprep, 256, [&](int first, unsigned n) {
     p.first = first;

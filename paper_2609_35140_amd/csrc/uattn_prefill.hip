@@ -51,13 +51,12 @@ struct PrefillParams {
   __bf16* out;
   float* lse;
   int hq, hkv, group, total;
-  int num_seqs, ngroups;  // work groups = (tile_group query tiles from the end, sequence, kv head)
-  int tile_group;         // query tiles to a work group
-  int first;              // workgroups of the launches before this one
+  XcdUnits units;  // of query tiles, counted from the sequence's end
+  int first;       // workgroups of the launches before this one
   float c;
 };
 
-// Workgroup order (xcd_unit): the G q heads and kTileGroup consecutive query
+// Workgroup order (xcd_tile): the G q heads and kTileGroup consecutive query
 // tiles of one (sequence, kv head) read the same K/V tiles from the sequence's
 // start on, so they run back to back on one XCD and share its L2; units go to
 // the XCDs in descending-cost order (query tiles counted from the end first).
@@ -219,12 +218,10 @@ __global__ __launch_bounds__(kWaves * 64, 1) void prefill_kernel(PrefillParams p
   using TL = TileLayout<D>;
   __shared__ __attribute__((aligned(1024))) __bf16 lds[2 * TL::kStageElems];
 
-  const XcdUnit unit = xcd_unit(p.first + blockIdx.x, p.tile_group * p.group);
-  if (unit.unit >= p.ngroups) return;
-  const int zrev = unit.unit / (p.num_seqs * p.hkv) * p.tile_group + unit.member / p.group;
-  const int seq = (unit.unit / p.hkv) % p.num_seqs;
-  const int kvh = unit.unit % p.hkv;
-  const int head = kvh * p.group + unit.member % p.group;
+  const XcdTile at = xcd_tile(p.first + blockIdx.x, p.units);
+  if (at.tile >= p.units.ntiles) return;
+  const int zrev = at.tile, seq = at.seq, kvh = at.kvh;
+  const int head = kvh * p.group + at.head;
   // clamp the (trusted) offsets so that a malformed table cannot index outside the tensors
   const int lo = min(max(p.cu[seq], 0), p.total);
   const int L = max(min(p.cu[seq + 1], p.total) - lo, 0);
@@ -438,12 +435,10 @@ __global__ __launch_bounds__(kWaves * 64, 1) void prefill_split_kernel(PrefillPa
   __shared__ float2 part_ml[2][kSplitRowGroups][kNB][kQCols];
   static_assert(kSplitRowGroups * kNB * NDH * 64 * 16 <= TL::kStageElems * 2, "a stream's half partials fit its stage");
 
-  const XcdUnit unit = xcd_unit(p.first + blockIdx.x, p.group);
-  if (unit.unit >= p.ngroups) return;
-  const int zrev = unit.unit / (p.num_seqs * p.hkv);
-  const int seq = (unit.unit / p.hkv) % p.num_seqs;
-  const int kvh = unit.unit % p.hkv;
-  const int head = kvh * p.group + unit.member;
+  const XcdTile at = xcd_tile(p.first + blockIdx.x, p.units);
+  if (at.tile >= p.units.ntiles) return;
+  const int zrev = at.tile, seq = at.seq, kvh = at.kvh;
+  const int head = kvh * p.group + at.head;
   const int lo = min(max(p.cu[seq], 0), p.total);
   const int L = max(min(p.cu[seq + 1], p.total) - lo, 0);
   const int qt = (L + kSplitRows - 1) / kSplitRows - 1 - zrev;
@@ -629,7 +624,6 @@ hipError_t launch_prefill(const PrefillLaunch& a, hipStream_t stream) {
   p.group = a.num_q_heads / a.num_kv_heads;
   p.total = a.total_tokens;
   p.c = a.c;
-  p.num_seqs = a.num_seqs;
   // Workgroups with rows in them, at most, for tiles of `rows` rows.
   const int64_t cus = device_cus();
   auto tiles = [&](int64_t rows) { return (static_cast<int64_t>(a.max_seqlen) + rows - 1) / rows; };
@@ -645,13 +639,9 @@ hipError_t launch_prefill(const PrefillLaunch& a, hipStream_t stream) {
   // 227 / 171; 32 of 128 keys, which fill half of a 256-row tile, 42.8 / 37.8.
   const bool split = a.max_seqlen <= kSplitRows || busy(kSplitRows) <= cus ||
                      (busy(kWgRows) <= cus && a.max_seqlen > 2 * kChunkKeys);
-  const int64_t units = static_cast<int64_t>(a.num_seqs) * a.num_kv_heads;
-  p.tile_group = split ? 1 : unit_tiles(tiles(kWgRows), busy(kWgRows), kTileRounds, kTileGroup);
-  const int64_t ngroups = (tiles(split ? kSplitRows : kWgRows) + p.tile_group - 1) / p.tile_group * units;
-  const int64_t nblocks = xcd_grid(ngroups, p.group * p.tile_group);
-  if (nblocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
-  p.ngroups = static_cast<int>(ngroups);
-  return launch_parts(nblocks, kWaves * 64, [&](int first, unsigned n) {
+  const int unit = split ? 1 : unit_tiles(tiles(kWgRows), busy(kWgRows), kTileRounds, kTileGroup);
+  p.units = xcd_units(tiles(split ? kSplitRows : kWgRows), unit, p.group, a.num_seqs, a.num_kv_heads);
+  return launch_parts(xcd_grid(p.units), kWaves * 64, [&](int first, unsigned n) {
     p.first = first;
     const dim3 grid(n), block(kWaves * 64);
     if (split && a.head_dim == 128)

@@ -24,15 +24,41 @@
 namespace uattn {
 
 // The hardware deals consecutive workgroup ids to the 8 XCDs in turn, and each
-// XCD has its own L2.  Work is cut into units whose `members` workgroups read
-// the same tiles; unit u runs on XCD u % 8, its members back to back.
+// XCD has its own L2.  Work is cut into units whose workgroups read the same
+// tiles: `tiles` consecutive query or key tiles of a stream (a sequence's kv
+// head) for each of `heads` heads.  Unit u runs on XCD u % 8, its members back
+// to back, tile by tile.
 constexpr int kXcds = 8;
-struct XcdUnit {
-  int unit, member;
+struct XcdUnits {
+  int tiles, heads;      // of a unit
+  int num_seqs, hkv;     // streams: kv head fastest
+  int ntiles;            // of a stream, the last unit's in full
 };
-__device__ __forceinline__ XcdUnit xcd_unit(int pid, int members) {
-  const int j = pid / kXcds;
-  return {j / members * kXcds + pid % kXcds, j % members};
+struct XcdTile {
+  int tile, head, seq, kvh;  // tile >= ntiles: nothing to do
+};
+// An XCD hands its workgroups to its four shader engines in turn, so with an even
+// number of tiles to a unit a tile of one place in its unit would always meet the
+// same engines, and a unit's tiles differ in cost (its last one may be empty).  So
+// each unit starts at another of its tiles: turn + turn / 2, whose sequence gives
+// every engine every place equally often for 2, 4, 6 and 8 tiles; an odd number
+// needs none.  Four sequences of 4096, 32/32 heads, units of four: 647 us from the
+// first tile on, 604 so (606 single tiles); 8 of 512-8192 1780, 1699 (1835).
+__device__ __forceinline__ XcdTile xcd_tile(int pid, const XcdUnits& u) {
+  const int j = pid / kXcds, members = u.tiles * u.heads;
+  const int turn = j / members, unit = turn * kXcds + pid % kXcds;
+  int head = j % members, t = 0;
+  while (head >= u.heads) {
+    head -= u.heads;
+    ++t;
+  }
+  if (u.tiles % 2 == 0) {
+    t += (turn + turn / 2) % 8;
+    while (t >= u.tiles) t -= u.tiles;
+  }
+  const int streams = u.num_seqs * u.hkv;
+  const int stream = unit % streams;
+  return {unit / streams * u.tiles + t, head, stream / u.hkv, stream % u.hkv};
 }
 // Workgroups with rows in them, at most, of a launch that cuts every sequence
 // (max_seqlen at most, total_tokens together) into tiles of `rows` rows, for
@@ -49,8 +75,14 @@ inline int unit_tiles(int64_t tiles, int64_t busy, int rounds, int most) {
   if (busy < static_cast<int64_t>(rounds) * device_cus()) return 1;
   return static_cast<int>(tiles < most ? tiles : most);
 }
-// Workgroups of a launch over `units` units (ids past the last unit do nothing).
-inline int64_t xcd_grid(int64_t units, int64_t members) { return (units + kXcds - 1) / kXcds * kXcds * members; }
+// Workgroups of a launch over `u` (ids past the last unit do nothing).
+inline int64_t xcd_grid(const XcdUnits& u) {
+  const int64_t units = static_cast<int64_t>(u.ntiles / u.tiles) * u.num_seqs * u.hkv;
+  return (units + kXcds - 1) / kXcds * kXcds * u.tiles * u.heads;
+}
+inline XcdUnits xcd_units(int64_t ntiles, int tiles, int heads, int num_seqs, int hkv) {
+  return {tiles, heads, num_seqs, hkv, static_cast<int>((ntiles + tiles - 1) / tiles * tiles)};
+}
 
 // 256 zero bytes; the source of every tile row past the context.
 __device__ __attribute__((aligned(256))) uint4 g_zero_rows[16];

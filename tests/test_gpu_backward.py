@@ -88,7 +88,8 @@ def test_matches_oracle(ua, lens, hq, hkv, d, sigma):
 
 
 # the dK/dV kernel's edges: a walk of one, two and three steps (its ring of three tiles), a sequence that ends a row
-# before, at and after a key tile (128) and a work unit (8 key tiles), kv head counts that do not divide the 8 XCDs
+# before, at and after a key tile (128), kv head counts that do not divide the 8 XCDs (all in single tiles; units of
+# several are test_units_of_several_tiles)
 TILE_EDGES = [
     ([1, 63, 64, 65, 127, 128, 129], 2, 1, 128, 1.0),
     ([1023, 1024, 1025], 3, 3, 64, 1.0),
@@ -117,6 +118,35 @@ def test_more_workgroups_than_one_grid(ua):
     got = ua.prefill_backward(q, k, v, out, do, lse, gu.dev_i32(inputs.cu_seqlens(spread)), 1280)
     for a, b in zip(got, want):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(15, 3, 128), (15, 3, 64), (13, 13, 64), (20, 5, 128)])
+def test_units_of_several_tiles(ua, hq, hkv, d):
+    """Packs large enough for units of 4 query tiles (forward), 8 key tiles and 2 query tiles, with streams that do not fill
+    the 8 XCDs evenly and 9 query and 17 key tiles, so the last unit of a stream is not full: every sequence's output,
+    log-sum-exp and gradients equal those of a call of its own, which takes single tiles."""
+    import torch
+    lens = [int(x) for x in inputs.rng(87, hq, d).integers(100, 2100, size=44)]
+    lens[3], lens[20] = 2100, 1
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    T = sum(lens)
+    assert (T // 256 + len(lens)) * hq >= 8 * cus and (T // 128 + len(lens)) * hkv >= 4 * cus
+    assert (2100 // 256 + 1) * hq < 8 * cus and (2100 // 128 + 1) * hkv < 4 * cus
+    q, do = (inputs.normal_bf16_device((T, hq, d), 1.0, 88, hq, d, i) for i in range(2))
+    k, v = (inputs.normal_bf16_device((T, hkv, d), 1.0, 89, hq, d, i) for i in range(2))
+    cu = inputs.cu_seqlens(lens)
+
+    def run(rows, cu, most):
+        x = [t[rows] for t in (q, k, v)]
+        out, lse = ua.prefill(*x, gu.dev_i32(cu), most, return_lse=True)
+        return (out, lse) + tuple(ua.prefill_backward(*x, out, do[rows], lse, gu.dev_i32(cu), most))
+
+    pack = run(slice(0, T), cu, 2100)
+    for lo, n in zip(cu[:-1], lens):
+        rows = slice(int(lo), int(lo) + n)
+        for name, a, b in zip(("out", "lse", "dq", "dk", "dv"), pack, run(rows, [0, n], n)):
+            as_int = torch.int32 if name == "lse" else torch.int16
+            assert torch.equal(a[rows].view(as_int), b.view(as_int)), (name, n)
 
 
 @pytest.mark.parametrize("n", [26000, 60000])
