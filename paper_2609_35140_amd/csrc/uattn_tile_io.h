@@ -29,10 +29,29 @@ namespace uattn {
 // head) for each of `heads` heads.  Unit u runs on XCD u % 8, its members back
 // to back, tile by tile.
 constexpr int kXcds = 8;
+// Division by a number that is fixed per launch: m = floor(2^32 / d) (2^32 - 1 for
+// d = 1), so the high half of n * m is the quotient or one less, for any 32-bit n.
+struct Divider {
+  uint32_t d, m;
+};
+struct DivMod {
+  int q, r;
+};
+inline Divider divider(int64_t d) {
+  return {static_cast<uint32_t>(d), d == 1 ? 0xFFFFFFFFu : static_cast<uint32_t>((int64_t{1} << 32) / d)};
+}
+__device__ __forceinline__ DivMod divide(uint32_t n, Divider by) {
+  uint32_t q = __umulhi(n, by.m), r = n - q * by.d;
+  if (r >= by.d) {
+    ++q;
+    r -= by.d;
+  }
+  return {static_cast<int>(q), static_cast<int>(r)};
+}
 struct XcdUnits {
-  int tiles, heads;      // of a unit
-  int num_seqs, hkv;     // streams: kv head fastest
-  int ntiles;            // of a stream, the last unit's in full
+  Divider members, streams, hkv;  // streams: kv head fastest
+  int tiles, heads;               // of a unit
+  int ntiles;                     // of a stream, the last unit's in full
 };
 struct XcdTile {
   int tile, head, seq, kvh;  // tile >= ntiles: nothing to do
@@ -44,10 +63,14 @@ struct XcdTile {
 // every engine every place equally often for 2, 4, 6 and 8 tiles; an odd number
 // needs none.  Four sequences of 4096, 32/32 heads, units of four: 647 us from the
 // first tile on, 604 so (606 single tiles); 8 of 512-8192 1780, 1699 (1835).
+// max_seqlen may be far above a sequence's length, so most workgroups of a launch may
+// find no tile here, and what they cost is these few lines in every wave: with the
+// compiler's divisions 2048 sequences of 16 tokens, max_seqlen 2048, 8/1 heads, d = 64
+// took 413 us, so 330 (361 with three divisions and no units).
 __device__ __forceinline__ XcdTile xcd_tile(int pid, const XcdUnits& u) {
-  const int j = pid / kXcds, members = u.tiles * u.heads;
-  const int turn = j / members, unit = turn * kXcds + pid % kXcds;
-  int head = j % members, t = 0;
+  const DivMod own = divide(pid / kXcds, u.members);
+  const int turn = own.q;
+  int head = own.r, t = 0;
   while (head >= u.heads) {
     head -= u.heads;
     ++t;
@@ -56,9 +79,8 @@ __device__ __forceinline__ XcdTile xcd_tile(int pid, const XcdUnits& u) {
     t += (turn + turn / 2) % 8;
     while (t >= u.tiles) t -= u.tiles;
   }
-  const int streams = u.num_seqs * u.hkv;
-  const int stream = unit % streams;
-  return {unit / streams * u.tiles + t, head, stream / u.hkv, stream % u.hkv};
+  const DivMod unit = divide(turn * kXcds + pid % kXcds, u.streams), stream = divide(unit.r, u.hkv);
+  return {unit.q * u.tiles + t, head, stream.q, stream.r};
 }
 // Workgroups with rows in them, at most, of a launch that cuts every sequence
 // (max_seqlen at most, total_tokens together) into tiles of `rows` rows, for
@@ -75,13 +97,14 @@ inline int unit_tiles(int64_t tiles, int64_t busy, int rounds, int most) {
   if (busy < static_cast<int64_t>(rounds) * device_cus()) return 1;
   return static_cast<int>(tiles < most ? tiles : most);
 }
+inline XcdUnits xcd_units(int64_t ntiles, int tiles, int heads, int num_seqs, int hkv) {
+  return {divider(static_cast<int64_t>(tiles) * heads), divider(static_cast<int64_t>(num_seqs) * hkv), divider(hkv), tiles,
+          heads, static_cast<int>((ntiles + tiles - 1) / tiles * tiles)};
+}
 // Workgroups of a launch over `u` (ids past the last unit do nothing).
 inline int64_t xcd_grid(const XcdUnits& u) {
-  const int64_t units = static_cast<int64_t>(u.ntiles / u.tiles) * u.num_seqs * u.hkv;
-  return (units + kXcds - 1) / kXcds * kXcds * u.tiles * u.heads;
-}
-inline XcdUnits xcd_units(int64_t ntiles, int tiles, int heads, int num_seqs, int hkv) {
-  return {tiles, heads, num_seqs, hkv, static_cast<int>((ntiles + tiles - 1) / tiles * tiles)};
+  const int64_t units = static_cast<int64_t>(u.ntiles / u.tiles) * u.streams.d;
+  return (units + kXcds - 1) / kXcds * kXcds * u.members.d;
 }
 
 // 256 zero bytes; the source of every tile row past the context.
