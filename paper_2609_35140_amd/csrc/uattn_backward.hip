@@ -724,10 +724,10 @@ hipError_t launch_backward_d(const BwdParams& p0, int max_seqlen, hipStream_t st
   BwdParams p = p0;
   const int64_t ktiles = (static_cast<int64_t>(max_seqlen) + kKeyTile - 1) / kKeyTile;
   const int64_t qtiles = (static_cast<int64_t>(max_seqlen) + kDqRows - 1) / kDqRows;
-  const int kt_group = unit_tiles(ktiles, busy_workgroups(max_seqlen, p.num_seqs, p.total, kKeyTile, p.hkv), kKeyTileRounds,
-                          kKeyTileGroup);
-  const int qt_group = unit_tiles(qtiles, busy_workgroups(max_seqlen, p.num_seqs, p.total, kDqRows, p.hq), kDqTileRounds,
-                          kDqTileGroup);
+  const int64_t busy_kv = busy_workgroups(max_seqlen, p.num_seqs, p.total, kKeyTile, p.hkv);
+  const int64_t busy_dq = busy_workgroups(max_seqlen, p.num_seqs, p.total, kDqRows, p.hq);
+  const int kt_group = unit_tiles(busy_kv, p.num_seqs, p.hkv, kKeyTileRounds, kKeyTileGroup);
+  const int qt_group = unit_tiles(busy_dq, p.num_seqs, p.hq, kDqTileRounds, kDqTileGroup);
   p.kv_units = xcd_units(ktiles, kt_group, 1, p.num_seqs, p.hkv);
   p.dq_units = xcd_units(qtiles, qt_group, p.group, p.num_seqs, p.hkv);
   const int64_t nkv = xcd_grid(p.kv_units), ndq = xcd_grid(p.dq_units);

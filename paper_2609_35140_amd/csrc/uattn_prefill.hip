@@ -639,7 +639,7 @@ hipError_t launch_prefill(const PrefillLaunch& a, hipStream_t stream) {
   // 227 / 171; 32 of 128 keys, which fill half of a 256-row tile, 42.8 / 37.8.
   const bool split = a.max_seqlen <= kSplitRows || busy(kSplitRows) <= cus ||
                      (busy(kWgRows) <= cus && a.max_seqlen > 2 * kChunkKeys);
-  const int unit = split ? 1 : unit_tiles(tiles(kWgRows), busy(kWgRows), kTileRounds, kTileGroup);
+  const int unit = split ? 1 : unit_tiles(busy(kWgRows), a.num_seqs, a.num_q_heads, kTileRounds, kTileGroup);
   p.units = xcd_units(tiles(split ? kSplitRows : kWgRows), unit, p.group, a.num_seqs, a.num_kv_heads);
   return launch_parts(xcd_grid(p.units), kWaves * 64, [&](int first, unsigned n) {
     p.first = first;
