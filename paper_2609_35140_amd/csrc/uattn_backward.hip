@@ -701,6 +701,15 @@ __device__ __forceinline__ void bwd_dq(const BwdParams& p, DqSmem<D>& sm, int pi
 // 6 sequences of 64-700 tokens, 16/4 heads, d = 64: 41.7 + 13.3 us in two
 // launches, 44.8 in one (forward and backward 72.2 -> 61.9); 8 of 512-8192,
 // 32/8 heads, d = 128: 4.40 ms either way.
+//
+// Except at d = 64 with many dQ workgroups (kDqApart to a CU) of sequences that on
+// average do not fill one: there a dQ workgroup alone has 32 KB of LDS and 163
+// registers, so the next one starts as the waves without rows end; behind the 82 KB
+// that dK/dV needs it cannot.  us in one launch and in two: 2048 sequences of 16
+// tokens, 8/1 heads (64 to a CU) 297 / 241, 1024 of 40, 8/2 (32) 175 / 146, 256 of
+// 128, 16/4 (16) 171 / 163; but 64 of 1-512, 16/4 (6) 176 / 182 and 40 of 1000, 16/4
+// (10) 509 / 553.
+constexpr int kDqApart = 8;
 static_assert(kKvWaves == kDqWaves, "one block size");
 template <int D>
 __global__ __launch_bounds__(kKvWaves * 64, 1) void bwd_grads_kernel(BwdParams p) {
@@ -714,6 +723,12 @@ __global__ __launch_bounds__(kKvWaves * 64, 1) void bwd_grads_kernel(BwdParams p
     bwd_dkdv<D>(p, sm.dkdv, pid);
   else
     bwd_dq<D>(p, sm.dq, pid - p.kv_blocks);  // kv_blocks is a multiple of the XCD count
+}
+
+template <int D>
+__global__ __launch_bounds__(kDqWaves * 64, 1) void bwd_dq_kernel(BwdParams p) {
+  __shared__ __attribute__((aligned(1024))) DqSmem<D> sm;
+  bwd_dq<D>(p, sm, p.first + blockIdx.x);
 }
 
 template <int D>
@@ -733,15 +748,27 @@ hipError_t launch_backward_d(const BwdParams& p0, int max_seqlen, hipStream_t st
   const int64_t nkv = xcd_grid(p.kv_units), ndq = xcd_grid(p.dq_units);
   if (nkv + ndq > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
   p.kv_blocks = static_cast<int>(nkv);
-  const hipError_t e = launch_parts(nprep, 256, [&](int first, unsigned n) {
+  hipError_t e = launch_parts(nprep, 256, [&](int first, unsigned n) {
     p.first = first;
     hipLaunchKernelGGL(bwd_prep_kernel<D>, dim3(n), dim3(256), 0, stream, p);
   });
   if (e != hipSuccess) return e;
-  return launch_parts(nkv + ndq, kKvWaves * 64, [&](int first, unsigned n) {
+  auto grads = [&](int first, unsigned n) {
     p.first = first;
     hipLaunchKernelGGL(bwd_grads_kernel<D>, dim3(n), dim3(kKvWaves * 64), 0, stream, p);
-  });
+  };
+  if constexpr (D == 64) {
+    const bool short_seqs = p.total < static_cast<int64_t>(p.num_seqs) * kDqRows;
+    if (short_seqs && busy_dq > static_cast<int64_t>(kDqApart) * device_cus()) {
+      e = launch_parts(nkv, kKvWaves * 64, grads);
+      if (e != hipSuccess) return e;
+      return launch_parts(ndq, kDqWaves * 64, [&](int first, unsigned n) {
+        p.first = first;
+        hipLaunchKernelGGL(bwd_dq_kernel<D>, dim3(n), dim3(kDqWaves * 64), 0, stream, p);
+      });
+    }
+  }
+  return launch_parts(nkv + ndq, kKvWaves * 64, grads);
 }
 
 }  // namespace

@@ -149,6 +149,28 @@ def test_units_of_several_tiles(ua, hq, hkv, d):
             assert torch.equal(a[rows].view(as_int), b.view(as_int)), (name, n)
 
 
+@pytest.mark.parametrize("hq,hkv,longest", [(16, 4, 200), (17, 1, 1300)])
+def test_many_short_sequences(ua, hq, hkv, longest):
+    """d = 64 and enough sequences, shorter than a query tile on average, for dQ in a launch of its own: every gradient
+    equals that of the sequence alone (one launch), empty sequences and one of several tiles among them."""
+    import torch
+    lens = [int(x) for x in inputs.rng(90, hq).integers(0, 200, size=150)]
+    lens[0], lens[70], lens[149] = 0, longest, 1
+    T = sum(lens)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert T < 256 * len(lens) and len(lens) * hq > 8 * cus
+    q, do = (inputs.normal_bf16_device((T, hq, 64), 1.0, 91, hq, i) for i in range(2))
+    k, v = (inputs.normal_bf16_device((T, hkv, 64), 1.0, 92, hq, i) for i in range(2))
+    cu = inputs.cu_seqlens(lens)
+    out, lse = ua.prefill(q, k, v, gu.dev_i32(cu), longest, return_lse=True)
+    pack = ua.prefill_backward(q, k, v, out, do, lse, gu.dev_i32(cu), longest)
+    for lo, n in zip(cu[:-1], lens):
+        rows = slice(int(lo), int(lo) + n)
+        alone = ua.prefill_backward(q[rows], k[rows], v[rows], out[rows], do[rows], lse[rows], gu.dev_i32([0, n]), n)
+        for a, b in zip(pack, alone):
+            assert torch.equal(a[rows].view(torch.int16), b.view(torch.int16)), n
+
+
 @pytest.mark.parametrize("n", [26000, 60000])
 def test_more_workgroups_than_one_grid(ua, n):
     """Mostly empty sequences, 32 kv heads and tiles for 1280 keys: 8.3 and 19 million dK/dV workgroups of 512 threads (more
