@@ -238,10 +238,11 @@ constexpr int kQTile = kTileKeys;                  // queries per step
 // step, so a unit's tiles come from its XCD's L2 (groups of 4, 16 and 32 were
 // within 2% of 8).
 constexpr int kKeyTileGroup = 8;
-// From this many workgroups to a CU on.  Below, forward and backward of equal
-// lengths lose by it (single tiles / eights, us: 24 of 1000, 16/4 heads, d = 64
-// 383 / 440; 10 of 1000, 32/8 heads, d = 128 485 / 511), though ragged packs may
-// still gain (16 of 200-2048, 32/8 heads 859 / 796).
+// From this many workgroups to a CU on.  Backward in single tiles / in eights, us:
+// 16 of 200-2048 tokens, 32/8 heads, d = 128 (5.5 to a CU) 1106 / 956, 8 of 512-4096,
+// 16/16 (12) 1194 / 1121, 16 of 1000, 32/8 (4.0) 573 / 576; d = 64, 24 of 1000, 16/4
+// (3.0) 282 / 298.  (Ragged packs gain below the line too: 10 of 200-2048, 32/8 heads
+// 511 / 484, 4 of 512-8192, 16/4, d = 64 1088 / 710.)
 constexpr int kKeyTileRounds = 4;
 
 // One matrix phase: acc[db][nb] += T^T w over the 64 rows of the tile at
@@ -533,7 +534,11 @@ constexpr int kDqNB = 2;
 constexpr int kDqWaveRows = kDqNB * kQCols;
 constexpr int kDqRows = kDqWaves * kDqWaveRows;
 constexpr int kDqTileGroup = 2;  // query tiles (of all the group's heads) to a work unit, see xcd_tile
-constexpr int kDqTileRounds = 8;  // the forward's line (kTileRounds); not measured apart
+// From this many workgroups to a CU on, as in the forward (kTileRounds).  Single / pairs,
+// us: 8 of 1000 tokens, 16/16 heads, d = 64 (2 to a CU) 111 / 116, 24 of 1000, 16/4 (6)
+// 280 / 285; d = 128, 8 of 512-4096, 32/32 (14) 2292 / 2259, 40/8 heads (16) 2628 /
+// 2611.  Between 8 and 14 both are within 1%.
+constexpr int kDqTileRounds = 8;
 
 template <int D>
 struct DqSmem {
@@ -741,7 +746,13 @@ hipError_t launch_backward_d(const BwdParams& p0, int max_seqlen, hipStream_t st
   const int64_t qtiles = (static_cast<int64_t>(max_seqlen) + kDqRows - 1) / kDqRows;
   const int64_t busy_kv = busy_workgroups(max_seqlen, p.num_seqs, p.total, kKeyTile, p.hkv);
   const int64_t busy_dq = busy_workgroups(max_seqlen, p.num_seqs, p.total, kDqRows, p.hq);
-  const int kt_group = unit_tiles(busy_kv, p.num_seqs, p.hkv, kKeyTileRounds, kKeyTileGroup);
+  // At d = 64 not for equal lengths (at least 5/6 of max_seqlen on average): half the
+  // bytes to share, and the long walks no longer start first.  Single tiles / eights:
+  // 40 of 1000, 16/4 heads 479 / 510, 32 of 2048 1267 / 1314, 30 of 1500-2048 (0.86)
+  // 998 / 1030; 20 of 2000-3000 (0.83) 1312 / 1297, 24 of 300-4000 1459 / 1336.
+  const bool equal = 6 * static_cast<int64_t>(p.total) >= 5 * static_cast<int64_t>(max_seqlen) * p.num_seqs;
+  const int kt_group =
+      D == 64 && equal ? 1 : unit_tiles(busy_kv, p.num_seqs, p.hkv, kKeyTileRounds, kKeyTileGroup);
   const int qt_group = unit_tiles(busy_dq, p.num_seqs, p.hq, kDqTileRounds, kDqTileGroup);
   p.kv_units = xcd_units(ktiles, kt_group, 1, p.num_seqs, p.hkv);
   p.dq_units = xcd_units(qtiles, qt_group, p.group, p.num_seqs, p.hkv);
