@@ -636,9 +636,13 @@ hipError_t launch_prefill(const PrefillLaunch& a, hipStream_t stream) {
   // Prefill_kernel against split, us (one sequence, 32/8 heads, d = 128): 128
   // keys 10.7 / 9.6, 512 22.7 / 15.8, 1000 36.7 / 25.3, 1536 51 / 38, 2048
   // 66 / 57, 3072 104 / 116; four of 300 keys 17.2 / 20.3; 8192, 8/1 heads
-  // 227 / 171; 32 of 128 keys, which fill half of a 256-row tile, 42.8 / 37.8.
-  const bool split = a.max_seqlen <= kSplitRows || busy(kSplitRows) <= cus ||
-                     (busy(kWgRows) <= cus && a.max_seqlen > 2 * kChunkKeys);
+  // 227 / 171; 32 of 128 keys, which fill half of a 256-row tile, 42.8 / 37.8.  A
+  // max_seqlen far above the average is taken for a bound and not for a chain: four of
+  // 300, max_seqlen 2048, 18.8 / 21.0; 8 of 200, 4096, 16/4 heads, d = 64 10.8 / 11.9.
+  const bool chain = a.max_seqlen > 2 * kChunkKeys &&
+                     a.max_seqlen <= 4 * static_cast<int64_t>(a.total_tokens) / a.num_seqs;
+  const bool split =
+      a.max_seqlen <= kSplitRows || busy(kSplitRows) <= cus || (busy(kWgRows) <= cus && chain);
   const int unit = split ? 1 : unit_tiles(busy(kWgRows), a.num_seqs, a.num_q_heads, kTileRounds, kTileGroup);
   p.units = xcd_units(tiles(split ? kSplitRows : kWgRows), unit, p.group, a.num_seqs, a.num_kv_heads);
   return launch_parts(xcd_grid(p.units), kWaves * 64, [&](int first, unsigned n) {
