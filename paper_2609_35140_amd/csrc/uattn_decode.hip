@@ -28,8 +28,9 @@
 // written to the workspace.
 //
 // The grid is persistent: as many workgroups as the CUs hold at once walk
-// the items in chunk-major order, stride = grid size; the length of the next
-// item's entry is read while the current item is computed.
+// the items in chunk-major order, stride = grid size (long walks a list of the
+// items that hold keys, entry by entry where the partials are buffered); the length
+// of the next item's entry is read while the current item is computed.
 //
 // Merge: finished partials are queued per workgroup and their arrivals are
 // counted when the queue is full and when the workgroup has no further
@@ -413,7 +414,10 @@ __global__ __launch_bounds__(256, kBuf ? 1 : 2) void decode_kernel(DecodeParams 
   // arrives last (8 steps of 8 x 8000 keys 461 us against 372).  Buffered walks,
   // which merge in a kernel of their own, list the pairs of an entry, whose
   // place takes fewer steps to find (4 steps of 8 x 32K keys, 64/8 heads: 844 us
-  // chunk by chunk, 834 so).
+  // chunk by chunk, 834 so).  There a workgroup's next item is one chunk further
+  // on in its entry than a grid's length would put it, or entries of two chunks
+  // would give some workgroups only the full and some only the last ones (256
+  // entries of 300 keys, 8/2 heads, d = 64: 23.6 us, 22.4 so; 21.9 without a list).
   // Batches past kListMax only drop the chunks past the longest entry.
   int ncand = ncand_all;
   const int nruns = kBuf ? p.batch : p.nchunk_max;
@@ -660,15 +664,27 @@ __global__ __launch_bounds__(256, kBuf ? 1 : 2) void decode_kernel(DecodeParams 
   // during the previous item (issued right after that item's V copies), so
   // every workgroup keeps one item's K rows in flight through the softmax
   // and PV phases.
+  // the workgroup's item after `it`, a grid's length on; in a buffered list also
+  // hkv items (one chunk) on within that stretch
+  const int turn = kList && kBuf ? p.hkv % stride : 0;
+  int place = blockIdx.x;  // of the last item handed out, in its stretch
+  auto after = [&](int it) {
+    if constexpr (!kList || !kBuf) return it + stride;
+    const int was = place, on = place + turn;
+    place = on < stride ? on : on - stride;
+    return it + stride + place - was;
+  };
   Desc desc = load_desc(blockIdx.x);
   Item cur = make_item(blockIdx.x, desc);
-  Desc desc_next = load_desc(in_grid(blockIdx.x + stride));
+  int item_next = after(blockIdx.x);
+  Desc desc_next = load_desc(in_grid(item_next));
   Operands op;
   issue_ops(cur, desc, op);
 #pragma unroll 1
-  for (int item = blockIdx.x; item < ncand; item += stride) {
-    const Item next = make_item(item + stride, desc_next);   // empty past the walk
-    const Desc desc_after = load_desc(in_grid(item + 2 * stride));
+  for (int item = blockIdx.x; item < ncand;) {
+    const Item next = make_item(item_next, desc_next);   // empty past the walk
+    const int item_after = after(item_next);
+    const Desc desc_after = load_desc(in_grid(item_after));
     const int tile = cur.chunk * kTilesPerChunk + wave;  // this wave's tile (sequence-relative)
     const bool tile_on = wave < cur.ntiles;
 
@@ -832,6 +848,8 @@ __global__ __launch_bounds__(256, kBuf ? 1 : 2) void decode_kernel(DecodeParams 
     cur = next;
     op = op_next;
     desc_next = desc_after;
+    item = item_next;
+    item_next = item_after;
   }
   // the end of the walk: count what is pending, and retire the last
   // (empty) operand prefetch
@@ -894,7 +912,9 @@ hipError_t launch_decode(const DecodeLaunch& a, hipStream_t stream) {
     };
     // The list of pairs with keys pays where a workgroup takes more than two
     // items of the grid: 16 entries of 400-3000 keys, 32/8 heads, 8 steps 220 us
-    // without it, 210 with; with all 16 at 3000 it costs 1% (283, 285.5).
+    // without it, 210 with.  Where nothing is empty it costs about 1% (16 of 3000,
+    // one step 35.0 / 35.6), and most where entries are many and short: 1024 of 200
+    // keys, max_seqlen 4096, 8/1 heads 30.8 / 32.9 (of 1-300 keys 48.7 / 46.4).
     // A shorter walk has too few items to earn the scan: 16 steps of 6 x 1824
     // keys, 64/8 heads, 239.4 us, 243.9 with the list's code in that kernel.
     const int64_t grid_list = grid_of(sizeof(DecodeSmem<kD, kNB, kBuf, true>));
