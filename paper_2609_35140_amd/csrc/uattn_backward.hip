@@ -217,16 +217,16 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(BwdParams p) {
 // Order: query tiles from the sequence's end down, the group's heads inside.
 // Every key tile of a (sequence, kv head) starts at the same query tile and
 // keeps step with the others, so the tiles that one of them brings into the
-// XCD's L2 serve all (from the diagonal up, heads outside, 86% of the L2
-// requests missed and the misses set the time: 4.2 ms against 3.0 in the
-// measurement below).
+// XCD's L2 serve all: 24% of the L2 requests of the whole launch (dQ with it)
+// miss, from the diagonal up with the heads outside 39%, and the backward of the
+// pack below takes 1-5% longer.
 //
-// What bounds it: the matrix phases (64 products, 1024 cycles at the issue
-// rate, against about 1.8 times that measured) with the other wave's vector
-// work beside them.  8 sequences of 512-8192 tokens, 32/8 heads, d = 128
-// (2.8 TFLOP in these four products): 4.85 ms with one wave per SIMD and
-// everything in it, 2.5-2.7 ms so (1.05-1.1 PFLOP/s).  Loads by waves 0-3 in
-// their matrix phase 2.8, in their vector phase 2.6 ms; the next phase's
+// What bounds it: the matrix phases with the other wave's vector work beside
+// them (matrix units busy 55% of the launch's cycles, dQ with it, on the pack
+// below, 60% on 8 x 32K, 64/8 heads).  8 sequences of 512-8192 tokens, 32/8
+// heads, d = 128 (2.8 TFLOP in these four products): 4.85 ms with one wave per
+// SIMD and everything in it, 2.5-2.7 ms so (1.05-1.1 PFLOP/s).  Loads by waves
+// 0-3 in their matrix phase 2.8, in their vector phase 2.6 ms; the next phase's
 // first operands read before the barrier 2.7 ms.
 // ---------------------------------------------------------------------------
 constexpr int kKvPairs = 4;                        // wave pairs, each with its own keys

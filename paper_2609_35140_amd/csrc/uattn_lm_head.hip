@@ -6,7 +6,8 @@
 // tiles for few tokens, see launch_rows); wave
 // (wm, wn) owns 64 vocab x 128 tokens (4 x 8 blocks), so each 16-byte LDS
 // operand read feeds 4 or 8 MFMAs.  K (the hidden dimension) is walked in
-// 64-wide chunks through a two-stage LDS ring filled by direct-to-LDS loads
+// 64-wide chunks (up to 256-wide in the small tiles) through a two-stage LDS ring
+// filled by direct-to-LDS loads
 // (16-byte pieces XOR-swizzled by row, so the lanes of an operand read's
 // LDS cycle hit distinct banks), and every accumulator steps K in ascending 32-wide MFMA
 // steps from zero: a row's logits never depend on the batch, its size or the
@@ -21,9 +22,10 @@
 // well as) storing the bf16 logits, the workgroup reduces each token's 256
 // logits of its vocab tile to a partial (max, sum of exp) pair and picks out
 // the target's logit when the target lies in the tile; a second kernel folds
-// each token's partials in ascending vocab-tile order.  Every reduction has
-// a structure fixed by vocab positions alone (lane, wave and tile order), so
-// a token's result does not depend on the batch or its place in it.
+// each token's partials in 16 runs of consecutive vocab tiles, ascending inside a
+// run, then run by run.  Every reduction has a structure fixed by vocab positions
+// alone (lane, wave, tile and run order), so a token's result does not depend on
+// the batch or its place in it.
 #include <type_traits>
 
 #include "uattn_internal.h"
@@ -52,7 +54,7 @@ struct LmHeadParams {
 };
 
 // VT vocab rows x TT tokens per workgroup, WM x WN waves (wave tile
-// VT/WM x TT/WN), a ring of STAGES chunks.
+// VT/WM x TT/WN), a ring of STAGES chunks of kKC hidden elements.
 template <int VT, int TT, int WM, int WN, int STAGES, int kKC>
 struct LmCfg {
   static constexpr int kPieces = kKC / 8;  // 16-byte pieces of a row's chunk
@@ -66,7 +68,7 @@ struct LmCfg {
   static_assert(kAInstr * 1024 * NW == VT * kKC * 2 && kBInstr * 1024 * NW == TT * kKC * 2, "chunk split");
   static constexpr int kChunkOps = kAInstr + kBInstr;
   struct Smem {
-    __bf16 a[STAGES][VT * kKC];   // weight rows, 128 bytes each, pieces swizzled
+    __bf16 a[STAGES][VT * kKC];   // weight rows, kKC elements each, pieces swizzled
     __bf16 b[STAGES][TT * kKC];   // hidden rows
   };
 };
@@ -192,7 +194,7 @@ __device__ __forceinline__ void lm_head_tile(const LmHeadParams& p, typename LmC
   const int wm = wave % WM, wn = wave / WM;
   const __bf16* zero = reinterpret_cast<const __bf16*>(g_zero_rows) + 8 * (lane & 15);
 
-  // chunk c (hidden elements 64c .. 64c+63) of this workgroup's rows into stage c % STAGES
+  // chunk c (hidden elements kKC*c .. kKC*c + kKC-1) of this workgroup's rows into stage c % STAGES
   auto issue_chunk = [&](int c) {
     const int k0 = c * kKC;
     __bf16* a = &sm.a[c % STAGES][0];
@@ -289,8 +291,8 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void lm_head_kernel(LmHeadParams p
 // valid one (their results are not written).
 // 4100 x 151,936 x 4096 (5.1 TFLOP): 4.60 ms with a chunk's reads before its
 // products, 4.19 so, 4.05 with the last 4 tokens in a tile of 64 instead of 256
-// (1.26 PFLOP/s).  Matrix units busy 68% of the cycles at 1.78 GHz: the clock
-// falls as they get busier.  Half of the L2 requests miss, but blocks of 4 x 8,
+// (1.26 PFLOP/s).  Matrix units busy 71% of the cycles at 1.73 GHz: the clock
+// falls as they get busier.  64% of the L2 requests miss, but blocks of 4 x 8,
 // 4 x 16 and 8 x 4 (vocab x token tiles) to an XCD instead of one vocab tile at
 // a time all take the same time.
 constexpr int kWideVT = kVocabTile, kWideTT = 256, kWideWM = 4, kWideWN = 2;
@@ -521,8 +523,8 @@ hipError_t launch_wide(LmHeadParams p, hipStream_t stream) {
 // Up to about 128 rows the product is bound by the stream of the weights
 // (1.24 GB for 151,936 x 4096: 190 us at the read ceiling), and a tile padded to
 // 256 tokens spends 345 us on it at 8 rows.  What the stream wants is bytes in
-// flight that a barrier does not drain, so two workgroups to a CU (80 KB of
-// LDS each), and long runs of a row per load: a power-of-two row length puts
+// flight that a barrier does not drain, so up to 64 rows two workgroups to a CU
+// (32 to 80 KB of LDS each), and long runs of a row per load: a power-of-two row length puts
 // the same chunk of all rows on few memory channels.  Measured at 8 rows,
 // 151,936 x 4096 (and with rows 128 bytes longer): 64 vocab rows x 256-wide
 // chunks 229 us (201), x 128 256 us (206) with 64 token columns; 256 vocab
@@ -531,6 +533,13 @@ hipError_t launch_wide(LmHeadParams p, hipStream_t stream) {
 // CU, 299 us (284).
 // The log-prob epilogue reduces 256 vocab entries in one workgroup, so its
 // shapes keep 256 rows.
+//
+// The lines at 64 and 128 rows, us at 151,936 x 4096 (fused): 64 rows 274 (288) in
+// tiles of 64, 65 rows 342 (342) in the tile of 128, whose 96 KB of LDS let one
+// workgroup to a CU, 128 rows 355 (344); 129 rows in the wide kernel 374 (375), in
+// two tiles of 128 401 (397).  The line at 64 is where the smaller tile ends and not
+// the best one: two 64-token tiles on one XCD take 306 (306) at 65 rows and 330
+// (319) at 128, a 128 x 128 tile, of which two fit a CU, 312 and 331.
 template <bool kLogprob>
 hipError_t launch_rows(const LmHeadParams& p, hipStream_t stream) {
   if constexpr (kLogprob) {

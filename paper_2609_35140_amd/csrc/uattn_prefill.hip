@@ -63,8 +63,10 @@ struct PrefillParams {
 // 16 sequences of 512-8192 tokens, 40/8 heads: 4.59 ms one tile at a time, 4.42
 // two, 4.27-4.37 four, 4.25-4.30 eight; 32/8 heads and 32K tokens within 1%.
 constexpr int kTileGroup = 4;
-// From this many workgroups to a CU on: 9 sequences of 352-5633 tokens, 8/1 heads
-// (3 to a CU), 188 us one tile at a time, 220 four.
+// From this many workgroups to a CU on.  One tile at a time / four, us: 9 sequences of
+// 352-5633 tokens, 8/1 heads (3.8 to a CU) 272 / 312, 8 of 1000, 16/16 (2) 56 / 71, 5
+// of 512-4096, 32/8 (7.5) 400 / 412; 8 of 512-4096, 40/8 (16) 889 / 862, 32 of 700,
+// 32/8 (12) 266 / 260.  Between 8 and 12 to a CU it is within 3% either way.
 constexpr int kTileRounds = 8;
 
 // Byte offset, from the address of the wave's first row, of the 16-byte
