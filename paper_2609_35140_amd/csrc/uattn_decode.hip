@@ -917,8 +917,17 @@ hipError_t launch_decode(const DecodeLaunch& a, hipStream_t stream) {
     // keys, max_seqlen 4096, 8/1 heads 30.8 / 32.9 (of 1-300 keys 48.7 / 46.4).
     // A shorter walk has too few items to earn the scan: 16 steps of 6 x 1824
     // keys, 64/8 heads, 239.4 us, 243.9 with the list's code in that kernel.
+    // And not where the walk merges by itself and a merge is long (chunks x heads to a
+    // kv head): in the plain grid of a few entries a workgroup's items are all of one
+    // entry and kv head, in the list of several, and the workgroup that arrives last
+    // merges them one after the other.  Plain / listed, us: 4 of 13577-27155 keys, 32/4
+    // heads, d = 128 (106 x 8) 48 / 57, 10 of 3000-12000, 136/8 (47 x 17) 132 / 156, 2 of
+    // 10000-40000, 32/8 (157 x 4) 57 / 62; 6 of 2000-20000, 40/8 (79 x 5) 44 / 38, 12 of
+    // 1000-4000, 136/8 (16 x 17) 54 / 51, 10 of 3000-12000, 32/8 (47 x 4) 73 / 69.
+    constexpr int kFusedMerge = 400;
+    const bool merges = kBuf || static_cast<int64_t>(a.nchunk_max) * p.group <= kFusedMerge;
     const int64_t grid_list = grid_of(sizeof(DecodeSmem<kD, kNB, kBuf, true>));
-    if (a.nchunk_max > 1 && a.nchunk_max <= kListRuns && a.batch <= kListMax && ncand > 2 * grid_list)
+    if (a.nchunk_max > 1 && a.nchunk_max <= kListRuns && a.batch <= kListMax && merges && ncand > 2 * grid_list)
       hipLaunchKernelGGL((decode_kernel<kD, kNB, kBuf, true>), dim3(static_cast<unsigned>(grid_list)), dim3(256), 0, stream,
                          p, p.seqlens, p.bt);
     else

@@ -398,14 +398,14 @@ def test_ragged_decode_walk_lists_every_chunk(ua, batch, hkv, group, d, longest)
     assert bool(torch.isfinite(out.float()).all()) and bool(torch.isfinite(lse).all())
 
 
-# up to 4096 items on 256 CUs the list is one of chunks, and more than 64 of them are several to a lane: 79, 65 (the last
-# lane's are not full) and 129 chunks, one and two query blocks; longer walks list entries: 12, 70 (two to a lane) and
-# 8 with more kv heads than workgroups
-@pytest.mark.parametrize("batch,hkv,group,d,longest", [(5, 8, 4, 128, 20000), (7, 8, 20, 64, 16640), (3, 8, 17, 64, 33024),
-                                                       (3, 8, 1, 128, 33024), (12, 8, 8, 128, 17000), (70, 8, 2, 64, 16640),
-                                                       (8, 260, 1, 64, 700)])
+# up to 4096 items on 256 CUs the list is one of chunks (while chunks x heads to a kv head are at most 400), and more than 64
+# of them are several to a lane: 79, 65 (the last lane's are not full) and 129 chunks, 4, 5, 3 and 1 heads; 98 x 17 takes no
+# list; longer walks list entries: 12, 70 (two to a lane) and 8 with more kv heads than workgroups
+@pytest.mark.parametrize("batch,hkv,group,d,longest", [(5, 8, 4, 128, 20000), (7, 8, 5, 64, 16640), (3, 8, 3, 64, 33024),
+                                                       (3, 8, 1, 128, 33024), (4, 4, 17, 128, 25000), (12, 8, 8, 128, 17000),
+                                                       (70, 8, 2, 64, 16640), (8, 260, 1, 64, 700)])
 def test_listed_walk_over_many_chunks(ua, batch, hkv, group, d, longest):
-    """Every entry of a listed walk equals itself alone, in a call short enough to take the plain grid."""
+    """Every entry of a long ragged walk equals itself alone, in a call short enough to take the plain grid."""
     import torch
     page = 64
     hq = hkv * group
