@@ -425,21 +425,45 @@ __global__ __launch_bounds__(256, kBuf ? 1 : 2) void decode_kernel(DecodeParams 
   int span = 1;      // runs to a lane
   int nch_lane = 0;  // kList: chunk count of entry `lane`
   if constexpr (kList) {
+    // a chunk's pairs: counted entry by entry, or past 64 entries from how many have
+    // how many chunks (998 entries of 75-601 keys, 17/1 heads, d = 64: 50 us entry by
+    // entry, 44 so; 199 of 1234, 4/2 31.6, 29.8).  hist[n]: entries of n chunks, hist[0] all
+    // with keys; in the place of the weights, which no wave writes before the first
+    // item's first barrier.
+    const bool by_hist = !kBuf && p.batch > 64;
+    int* const hist = reinterpret_cast<int*>(&sm.pw[0][0][0][0]);
+    static_assert(sizeof(sm.pw) >= (kListRuns + 1) * sizeof(int), "room for the counts");
+    if (by_hist) {
+      for (int i = tid; i <= nruns; i += 256) hist[i] = 0;
+      __syncthreads();
+    }
     for (int e = tid; e < (p.batch + 63) / 64 * 64; e += 256) {
       const int n = e < p.batch ? min(p.seqlens[e], p.max_seqlen) : 0;
-      sm.nch[e] = static_cast<uint16_t>(n > 0 ? (n + kChunkKeys - 1) / kChunkKeys : 0);
+      const int nch = n > 0 ? (n + kChunkKeys - 1) / kChunkKeys : 0;
+      sm.nch[e] = static_cast<uint16_t>(nch);
+      if (by_hist && nch > 0) {
+        atomicAdd(&hist[nch], 1);
+        atomicAdd(&hist[0], 1);
+      }
     }
     __syncthreads();
     nch_lane = sm.nch[lane];
     // every wave computes the same prefix for itself (64 runs at a time)
     // and writes the same words, so no barrier is needed before it reads them
     int total = 0;
+    int done = 0;  // by_hist: entries whose last chunk is before run r0
 #pragma unroll 1
     for (int r0 = 0; r0 < nruns; r0 += 64) {
       const uint32_t run = r0 + lane;
       int mine = 0;  // the run's pairs
       if constexpr (kBuf) {
         mine = sm.nch[run];
+      } else if (by_hist) {
+        const bool in = run < static_cast<uint32_t>(nruns);
+        const int last = in ? hist[run + 1] : 0;  // entries whose last chunk this is
+        const int through = done + wave_inclusive_sum(last);
+        mine = in ? hist[0] - (through - last) : 0;
+        done = __builtin_amdgcn_readlane(through, 63);
       } else {
         for (int e = 0; e < p.batch; e += 8) {
           const u32x4 v = *reinterpret_cast<const u32x4*>(&sm.nch[e]);
