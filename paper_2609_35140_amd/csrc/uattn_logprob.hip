@@ -129,9 +129,11 @@ __global__ __launch_bounds__(kThreads) void logprob_kernel(const uint16_t* __res
 //   1,000     64 x 4   2.7 / 28     256 x 1   2.8 / 63     1024 x 5   3.5 / 283
 //   2,048    128 x 4   2.9 / 52     256 x 4   2.9 / 81      64 x 4    3.1 / 45
 //   16,384   256 x 4   4.0 / 40.7   512 x 5   3.8 / 41.6   1024 x 5   4.3 / 56
+//   28,000   256 x 4   5.2 / 79     512 x 5   4.6 / 82     256 x 1   5.6 / 78
+//   32,000   512 x 5   4.9 / 89.5   256 x 4   5.5 / 90.5   256 x 1   6.2 / 90
 //   50,257   512 x 5   6.2 / 135    256 x 4   7.4 / 142    1024 x 5   6.3 / 147
 //   151,936 1024 x 5  11.5 / 407    512 x 5  12.4 / 412     256 x 1  19 / 424
-// The vectors of a thread stay between one and about sixteen.
+// The vectors of a thread stay between one and about twenty.
 hipError_t launch_logprob(const LogprobLaunch& a, hipStream_t stream) {
   const float k = static_cast<float>(static_cast<double>(a.inv_temperature) * 1.4426950408889634);
   auto launch = [&](auto threads_const, auto batch_const) {
@@ -145,7 +147,7 @@ hipError_t launch_logprob(const LogprobLaunch& a, hipStream_t stream) {
   using std::integral_constant;
   if (a.vocab <= 1024) return launch(integral_constant<int, 64>{}, integral_constant<int, 4>{});
   if (a.vocab <= 2048) return launch(integral_constant<int, 128>{}, integral_constant<int, 4>{});
-  if (a.vocab <= 16384) return launch(integral_constant<int, 256>{}, integral_constant<int, 4>{});
+  if (a.vocab <= 28672) return launch(integral_constant<int, 256>{}, integral_constant<int, 4>{});
   if (a.vocab <= 65536) return launch(integral_constant<int, 512>{}, integral_constant<int, 5>{});
   return launch(integral_constant<int, 1024>{}, integral_constant<int, 5>{});
 }
