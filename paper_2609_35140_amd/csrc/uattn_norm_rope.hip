@@ -11,6 +11,8 @@
 // produce identical rows.
 #include <math.h>
 
+#include <type_traits>
+
 #include "uattn_internal.h"
 #include "uattn_numerics.h"
 
@@ -91,10 +93,11 @@ __device__ __forceinline__ void round_pairs(float (&y)[8]) {
 // rows of kAhead items are requested before the first is used.
 // 39,855 tokens, 32/8 heads, d = 128: 168 us with about 230 instructions, LDS
 // shuffles and a pass at a time, 163 with the loads ahead alone, 140 so (5.8 TB/s);
-// one token 4.1 -> 2.8 us.
-constexpr int kAhead = 3;
+// one token 4.1 -> 2.8 us.  A token of fewer items is handled by as many as its
+// waves have (launch_qk_norm_rope): 9818 tokens, 12/12 heads, d = 64 (one to a wave)
+// 21.7 us as three, 19.2 as one.
 constexpr int kNormWaves = 4;
-template <int D>
+template <int D, int kAhead>
 __global__ __launch_bounds__(kNormWaves * 64) void qk_norm_rope_kernel(NormRopeParams p) {
   constexpr int LPR = D / 8;          // lanes per row
   constexpr int RPI = 64 / LPR;       // rows per item
@@ -234,10 +237,24 @@ hipError_t launch_qk_norm_rope(const NormRopeLaunch& a, hipStream_t stream) {
   // one workgroup per token
   return launch_parts(a.num_tokens, kNormWaves * 64, [&](int first, unsigned n) {
     p.first = first;
+    auto launch = [&](auto d_const, auto ahead_const) {
+      hipLaunchKernelGGL((qk_norm_rope_kernel<decltype(d_const)::value, decltype(ahead_const)::value>), dim3(n),
+                         dim3(kNormWaves * 64), 0, stream, p);
+    };
+    auto pick = [&](auto d_const) {
+      constexpr int kRows = 64 / (decltype(d_const)::value / 8);  // of an item
+      const int items = (p.hq + kRows - 1) / kRows + (p.hkv + kRows - 1) / kRows;
+      if (items <= kNormWaves)
+        launch(d_const, std::integral_constant<int, 1>{});
+      else if (items <= 2 * kNormWaves)
+        launch(d_const, std::integral_constant<int, 2>{});
+      else
+        launch(d_const, std::integral_constant<int, 3>{});
+    };
     if (a.head_dim == 128)
-      hipLaunchKernelGGL(qk_norm_rope_kernel<128>, dim3(n), dim3(kNormWaves * 64), 0, stream, p);
+      pick(std::integral_constant<int, 128>{});
     else
-      hipLaunchKernelGGL(qk_norm_rope_kernel<64>, dim3(n), dim3(kNormWaves * 64), 0, stream, p);
+      pick(std::integral_constant<int, 64>{});
   });
 }
 

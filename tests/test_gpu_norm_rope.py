@@ -68,10 +68,11 @@ def test_matches_oracle(ua, T, hq, hkv, d, sigma, eps):
     torch.cuda.synchronize()
 
 
-@pytest.mark.parametrize("T,hq,hkv,d", [(160, 1, 1, 64), (160, 7, 3, 128), (160, 9, 1, 64), (96, 50, 5, 128), (160, 97, 1, 64)])
+@pytest.mark.parametrize("T,hq,hkv,d", [(160, 1, 1, 64), (160, 7, 3, 128), (160, 9, 1, 64), (96, 50, 5, 128), (160, 97, 1, 64),
+                                         (96, 20, 4, 128), (96, 16, 16, 128), (160, 33, 1, 64)])
 def test_head_counts_match_oracle(ua, T, hq, hkv, d):
     """Items of 4 (d 128) or 8 (d 64) head rows that the heads do not fill, waves without an item, and more than one and
-    two rounds of three items to a wave.  A normalized value one bf16 unit apart (at most 2^-7 of it) moves the rotated
+    two rounds of three items to a wave, and tokens of up to four, eight and more items.  A normalized value one bf16 unit apart (at most 2^-7 of it) moves the rotated
     pair by at most that part of its length, which the rotation keeps, and rounding the result adds half as much."""
     x = {n: inputs.normal_bf16((T, h, d), 1.0, 74, T, n) for n, h in enumerate((hq, hkv))}
     w = {n: inputs.normal_bf16((d,), 1.0, 76, T, n) for n in range(2)}
