@@ -146,7 +146,7 @@ hipError_t launch_logprob(const LogprobLaunch& a, hipStream_t stream) {
   };
   using std::integral_constant;
   if (a.vocab <= 1024) return launch(integral_constant<int, 64>{}, integral_constant<int, 4>{});
-  if (a.vocab <= 2048) return launch(integral_constant<int, 128>{}, integral_constant<int, 4>{});
+  if (a.vocab <= 3072) return launch(integral_constant<int, 128>{}, integral_constant<int, 4>{});
   if (a.vocab <= 28672) return launch(integral_constant<int, 256>{}, integral_constant<int, 4>{});
   if (a.vocab <= 65536) return launch(integral_constant<int, 512>{}, integral_constant<int, 5>{});
   return launch(integral_constant<int, 1024>{}, integral_constant<int, 5>{});

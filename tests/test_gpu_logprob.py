@@ -106,7 +106,7 @@ def test_logprob_vocab_edges(ua, V):
     assert abs(got[2]) <= 2.0 ** -24 * abs(m[2]) + 2.0 ** -24
 
 
-@pytest.mark.parametrize("V", [512, 520, 1024, 1025, 2048, 2056, 8200, 16384, 20480, 28672, 28679, 65536, 65544])
+@pytest.mark.parametrize("V", [512, 520, 1024, 1025, 3072, 3080, 8200, 16384, 20480, 28672, 28679, 65536, 65544])
 def test_logprob_block_sizes(ua, V):
     """The steps of the workgroup's size by the vocabulary, and a full batch of loads and one vector more at each size: the
     oracle's value (masked rows as above), the same bits in any number of rows."""
