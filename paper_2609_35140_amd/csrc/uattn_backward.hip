@@ -708,12 +708,12 @@ __device__ __forceinline__ void bwd_dq(const BwdParams& p, DqSmem<D>& sm, int pi
 // 32/8 heads, d = 128: 4.40 ms either way.
 //
 // Except at d = 64 with many dQ workgroups (kDqApart to a CU) of sequences that on
-// average do not fill one: there a dQ workgroup alone has 32 KB of LDS and 163
+// average fill at most half of one: there a dQ workgroup alone has 32 KB of LDS and 163
 // registers, so the next one starts as the waves without rows end; behind the 82 KB
 // that dK/dV needs it cannot.  us in one launch and in two: 2048 sequences of 16
 // tokens, 8/1 heads (64 to a CU) 297 / 241, 1024 of 40, 8/2 (32) 175 / 146, 256 of
-// 128, 16/4 (16) 171 / 163; but 64 of 1-512, 16/4 (6) 176 / 182 and 40 of 1000, 16/4
-// (10) 509 / 553.
+// 128, 16/4 (16) 171 / 163; but 53 of 119-238, 40/5 (8) 153 / 164, 64 of 1-512, 16/4
+// (6) 176 / 182 and 40 of 1000, 16/4 (10) 509 / 553.
 constexpr int kDqApart = 8;
 static_assert(kKvWaves == kDqWaves, "one block size");
 template <int D>
@@ -769,7 +769,7 @@ hipError_t launch_backward_d(const BwdParams& p0, int max_seqlen, hipStream_t st
     hipLaunchKernelGGL(bwd_grads_kernel<D>, dim3(n), dim3(kKvWaves * 64), 0, stream, p);
   };
   if constexpr (D == 64) {
-    const bool short_seqs = p.total < static_cast<int64_t>(p.num_seqs) * kDqRows;
+    const bool short_seqs = 2 * static_cast<int64_t>(p.total) <= static_cast<int64_t>(p.num_seqs) * kDqRows;
     if (short_seqs && busy_dq > static_cast<int64_t>(kDqApart) * device_cus()) {
       e = launch_parts(nkv, kKvWaves * 64, grads);
       if (e != hipSuccess) return e;

@@ -151,14 +151,14 @@ def test_units_of_several_tiles(ua, hq, hkv, d):
 
 @pytest.mark.parametrize("hq,hkv,longest", [(16, 4, 200), (17, 1, 1300)])
 def test_many_short_sequences(ua, hq, hkv, longest):
-    """d = 64 and enough sequences, shorter than a query tile on average, for dQ in a launch of its own: every gradient
+    """d = 64 and enough sequences, at most half a query tile long on average, for dQ in a launch of its own: every gradient
     equals that of the sequence alone (one launch), empty sequences and one of several tiles among them."""
     import torch
     lens = [int(x) for x in inputs.rng(90, hq).integers(0, 200, size=150)]
     lens[0], lens[70], lens[149] = 0, longest, 1
     T = sum(lens)
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    assert T < 256 * len(lens) and len(lens) * hq > 8 * cus
+    assert 2 * T <= 256 * len(lens) and len(lens) * hq > 8 * cus
     q, do = (inputs.normal_bf16_device((T, hq, 64), 1.0, 91, hq, i) for i in range(2))
     k, v = (inputs.normal_bf16_device((T, hkv, 64), 1.0, 92, hq, i) for i in range(2))
     cu = inputs.cu_seqlens(lens)
