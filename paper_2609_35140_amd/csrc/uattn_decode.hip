@@ -41,6 +41,7 @@
 // full-sequence kernel applies at its chunk boundaries.  Chunk boundaries
 // depend only on key positions, so nothing here depends on the batch, its
 // order, the grid, max_seqlen or which workgroup merges.
+#include <numeric>
 #include <type_traits>
 
 #include "uattn_internal.h"
@@ -64,6 +65,7 @@ struct DecodeParams {
   int batch, hq, hkv, group, maxp, page_size, page_shift, num_pages, max_seqlen, nchunk_max;
   int nslot;         // partial slots per (entry, q head): nchunk_max rounded up to even
   int first;         // decode_merge_kernel: workgroups of the launches before this one
+  int turn;          // buffered list: below the grid's size
   float c;
 };
 
@@ -414,10 +416,11 @@ __global__ __launch_bounds__(256, kBuf ? 1 : 2) void decode_kernel(DecodeParams 
   // arrives last (8 steps of 8 x 8000 keys 461 us against 372).  Buffered walks,
   // which merge in a kernel of their own, list the pairs of an entry, whose
   // place takes fewer steps to find (4 steps of 8 x 32K keys, 64/8 heads: 844 us
-  // chunk by chunk, 834 so).  There a workgroup's next item is one chunk further
-  // on in its entry than a grid's length would put it, or entries of two chunks
-  // would give some workgroups only the full and some only the last ones (256
-  // entries of 300 keys, 8/2 heads, d = 64: 23.6 us, 22.4 so; 21.9 without a list).
+  // chunk by chunk, 834 so).  There a workgroup's next item may be a few chunks
+  // further on in its entry than a grid's length would put it (p.turn), or equal
+  // entries would give some workgroups only full chunks and some only the last, short
+  // ones (256 entries of 300 keys, 8/2 heads, d = 64: 23.6 us, 22.4 so; 21.9 without a
+  // list).
   // Batches past kListMax only drop the chunks past the longest entry.
   int ncand = ncand_all;
   const int nruns = kBuf ? p.batch : p.nchunk_max;
@@ -689,8 +692,8 @@ __global__ __launch_bounds__(256, kBuf ? 1 : 2) void decode_kernel(DecodeParams 
   // every workgroup keeps one item's K rows in flight through the softmax
   // and PV phases.
   // the workgroup's item after `it`, a grid's length on; in a buffered list also
-  // hkv items (one chunk) on within that stretch
-  const int turn = kList && kBuf ? p.hkv % stride : 0;
+  // p.turn items on within that stretch
+  const int turn = kList && kBuf ? p.turn : 0;
   int place = blockIdx.x;  // of the last item handed out, in its stretch
   auto after = [&](int it) {
     if constexpr (!kList || !kBuf) return it + stride;
@@ -951,6 +954,14 @@ hipError_t launch_decode(const DecodeLaunch& a, hipStream_t stream) {
     constexpr int kFusedMerge = 400;
     const bool merges = kBuf || static_cast<int64_t>(a.nchunk_max) * p.group <= kFusedMerge;
     const int64_t grid_list = grid_of(sizeof(DecodeSmem<kD, kNB, kBuf, true>));
+    // A stretch of the grid's length moves a buffered list's walk by grid / hkv chunks
+    // of its entries, and by `on` more, the fewest after which entries of the largest
+    // chunk count (or of a divisor of it) meet each of their chunks equally often: 4
+    // chunks, 8 kv heads, 256 workgroups 1, 11 chunks 0 (one more would bring every
+    // workgroup back to the same one: 82 entries of 2714 keys 156 us, 160).
+    int on = 0;
+    while (std::gcd(grid_list / a.num_kv_heads + on, static_cast<int64_t>(a.nchunk_max)) > 1) ++on;
+    p.turn = static_cast<int>(static_cast<int64_t>(on) * a.num_kv_heads % grid_list);
     if (a.nchunk_max > 1 && a.nchunk_max <= kListRuns && a.batch <= kListMax && merges && ncand > 2 * grid_list)
       hipLaunchKernelGGL((decode_kernel<kD, kNB, kBuf, true>), dim3(static_cast<unsigned>(grid_list)), dim3(256), 0, stream,
                          p, p.seqlens, p.bt);
