@@ -51,6 +51,7 @@ __device__ __forceinline__ DivMod divide(uint32_t n, Divider by) {
 struct XcdUnits {
   Divider members, streams, hkv;  // streams: kv head fastest
   int tiles, heads;               // of a unit
+  int rotate;                     // units start at different tiles of theirs (see xcd_tile)
   int ntiles;                     // of a stream, the last unit's in full
 };
 struct XcdTile {
@@ -61,8 +62,9 @@ struct XcdTile {
 // same engines, and a unit's tiles differ in cost (its last one may be empty).  So
 // each unit starts at another of its tiles: turn + turn / 2, whose sequence gives
 // every engine every place equally often for 2, 4, 6 and 8 tiles; an odd number
-// needs none.  Four sequences of 4096, 32/32 heads, units of four: 647 us from the
-// first tile on, 604 so (606 single tiles); 8 of 512-8192 1780, 1699 (1835).
+// needs none, nor do four or eight heads to a tile.  Four sequences of 4096, 32/32
+// heads, units of four: 647 us from the first tile on, 604 so (606 single tiles); 8 of
+// 512-8192 1780, 1699 (1835).
 // max_seqlen may be far above a sequence's length, so most workgroups of a launch may
 // find no tile here, and what they cost is these few lines in every wave: with the
 // compiler's divisions 2048 sequences of 16 tokens, max_seqlen 2048, 8/1 heads, d = 64
@@ -75,7 +77,7 @@ __device__ __forceinline__ XcdTile xcd_tile(int pid, const XcdUnits& u) {
     head -= u.heads;
     ++t;
   }
-  if (u.tiles % 2 == 0) {
+  if (u.rotate) {
     t += (turn + turn / 2) % 8;
     while (t >= u.tiles) t -= u.tiles;
   }
@@ -101,9 +103,9 @@ inline int unit_tiles(int64_t busy, int64_t num_seqs, int64_t heads, int rounds,
   const int64_t tiles = busy / (num_seqs * heads);
   return static_cast<int>(tiles < 1 ? 1 : tiles < most ? tiles : most);
 }
-inline XcdUnits xcd_units(int64_t ntiles, int tiles, int heads, int num_seqs, int hkv) {
+inline XcdUnits xcd_units(int64_t ntiles, int tiles, int heads, int num_seqs, int hkv, bool rotate = true) {
   return {divider(static_cast<int64_t>(tiles) * heads), divider(static_cast<int64_t>(num_seqs) * hkv), divider(hkv), tiles,
-          heads, static_cast<int>((ntiles + tiles - 1) / tiles * tiles)};
+          heads, rotate && tiles % 2 == 0 && heads % 4 != 0, static_cast<int>((ntiles + tiles - 1) / tiles * tiles)};
 }
 // Workgroups of a launch over `u` (ids past the last unit do nothing).
 inline int64_t xcd_grid(const XcdUnits& u) {
