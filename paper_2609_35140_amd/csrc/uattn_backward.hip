@@ -217,12 +217,12 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(BwdParams p) {
 // Order: query tiles from the sequence's end down, the group's heads inside.
 // Every key tile of a (sequence, kv head) starts at the same query tile and
 // keeps step with the others, so the tiles that one of them brings into the
-// XCD's L2 serve all: 24% of the L2 requests of the whole launch (dQ with it)
-// miss, from the diagonal up with the heads outside 39%, and the backward of the
-// pack below takes 1-5% longer.
+// XCD's L2 serve all: 20% of the L2 requests of the whole launch (dQ with it)
+// miss on the pack below.  (With units that start at different tiles 24%, and 39%
+// from the diagonal up with the heads outside, the backward 1-5% slower.)
 //
 // What bounds it: the matrix phases with the other wave's vector work beside
-// them (matrix units busy 55% of the launch's cycles, dQ with it, on the pack
+// them (matrix units busy 54% of the launch's cycles, dQ with it, on the pack
 // below, 60% on 8 x 32K, 64/8 heads).  8 sequences of 512-8192 tokens, 32/8
 // heads, d = 128 (2.8 TFLOP in these four products): 4.85 ms with one wave per
 // SIMD and everything in it, 2.5-2.7 ms so (1.05-1.1 PFLOP/s).  Loads by waves
